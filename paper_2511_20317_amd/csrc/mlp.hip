@@ -4,18 +4,15 @@
 //   z1 = X W1 + b1, h1 = bf16(relu(z1)); z2 = h1 W2 + b2, h2 = bf16(relu(z2));
 //   logit = h2 . w3 + b3;  loss = mean(softplus(logit) - y logit)
 //
-// The three dense products of the forward pass and the three of the backward
-// pass run through one tiled GEMM kernel (64x128 output tile per workgroup,
-// four wavefronts of 32x64 on v_mfma_f32_32x32x16_bf16, K staged through LDS
-// 64 at a time) with fused epilogues: bias + ReLU + bf16 rounding (forward),
-// ReLU mask + bf16 rounding (backpropagated deltas), plain fp32 (weight
-// gradients).
+// Three kernels carry it.  fwd_kernel runs the whole forward pass of a block
+// of rows (two layers on v_mfma_f32_32x32x16_bf16 and the logit) with the
+// hidden rows kept in LDS; delta_kernel the loss derivative and the delta of
+// the first layer; grad_kernel every weight gradient and the loss.
 #include <hip/hip_runtime.h>
 
 #include "../../include/tsf.h"
 #include "tsf_internal.h"
 
-#include <cstring>
 
 namespace {
 
@@ -46,329 +43,635 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-enum Epilogue { EP_BIAS_RELU_BF16 = 0, EP_MASK_BF16 = 1, EP_F32 = 2 };
-
-struct GemmArgs {
-    // C[m][n] = sum_k A(m,k) B(n,k); element (r,c) of an operand at
-    // ptr[r * s_row + c * s_col] (bf16)
-    const uint16_t *A;
-    int64_t a_row, a_col;
-    const uint16_t *B;
-    int64_t b_row, b_col;
-    int M, N, K;
-    int ep;
-    const float *bias;      // EP_BIAS_RELU_BF16: N
-    const uint16_t *mask;   // EP_MASK_BF16: M x N, row-major (keep where > 0)
-    uint16_t *out_bf16;     // M x N row-major
-    float *out_f32;         // M x N row-major
-};
-
 typedef __bf16 v8bf16 __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf16 __attribute__((ext_vector_type(2)));
+typedef float v2f32 __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 
-// Output tile BM x BN per workgroup of four wavefronts (2 x 2 of WM x 64);
-// K is staged through LDS 64 at a time.
-constexpr int BM = 64, BN = 128, BK = 64, LDK = BK + 8;
-// wavefront sub-tile: WM x 64, AM blocks of 32 rows
-constexpr int WM = BM / 2, AM = WM / 32;
-
-// Stage a 128 x BK tile of an operand (rows r0.., cols k0..) into LDS as
-// tile[r][k], zero outside the matrix.  When the operand's k is contiguous,
-// each thread moves 8 consecutive elements (16 bytes) at a time; otherwise
-// threads walk the contiguous row dimension so reads still coalesce.
-template <int R>
-__device__ __forceinline__ void stage(uint16_t (*tile)[LDK], const uint16_t *P, int64_t s_row,
-                                      int64_t s_col, int rows, int K, int r0, int k0)
+// two floats to packed bf16, to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    const int tid = threadIdx.x;
-    if (s_col == 1) {
-        for (int e = tid; e < R * BK / 8; e += 256) {
-            const int r = e / (BK / 8), kc = (e % (BK / 8)) * 8;
-            const int gr = r0 + r, gk = k0 + kc;
-            const uint16_t *src = P + gr * s_row + gk;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (gr < rows) {
-                if (gk + 8 <= K && ((reinterpret_cast<uintptr_t>(src) & 15) == 0)) {
-                    v = *reinterpret_cast<const uint4 *>(src);
-                } else {
-                    uint16_t tmp[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) tmp[q] = (gk + q < K) ? src[q] : (uint16_t)0;
-                    v = make_uint4(tmp[0] | (uint32_t)tmp[1] << 16, tmp[2] | (uint32_t)tmp[3] << 16,
-                                   tmp[4] | (uint32_t)tmp[5] << 16, tmp[6] | (uint32_t)tmp[7] << 16);
-                }
-            }
-            *reinterpret_cast<uint4 *>(&tile[r][kc]) = v;
-        }
+    const v2f32 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf16));
+}
+
+// eight consecutive bf16 of global memory; AL: p is 16-byte aligned
+template <bool AL>
+__device__ __forceinline__ v4u32 load8(const uint16_t *p)
+{
+    if constexpr (AL) {
+        return *reinterpret_cast<const v4u32 *>(p);
     } else {
-        for (int e = tid; e < R * BK; e += 256) {
-            const int k = e / R, r = e % R;
-            const int gr = r0 + r, gk = k0 + k;
-            tile[r][k] = (gr < rows && gk < K) ? P[gr * s_row + gk * s_col] : (uint16_t)0;
+        return v4u32{p[0] | (uint32_t)p[1] << 16, p[2] | (uint32_t)p[3] << 16,
+                     p[4] | (uint32_t)p[5] << 16, p[6] | (uint32_t)p[7] << 16};
+    }
+}
+template <bool AL>
+__device__ __forceinline__ void store8(uint16_t *p, v4u32 v)
+{
+    if constexpr (AL) {
+        *reinterpret_cast<v4u32 *>(p) = v;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            p[2 * q] = (uint16_t)v[q];
+            p[2 * q + 1] = (uint16_t)(v[q] >> 16);
         }
     }
 }
 
-// The same staging split in two for operands whose k is contiguous: each
-// thread's two 16-byte pieces of the next tile are read into registers while
-// the current tile is multiplied, then written to LDS.
-template <int R>
-struct Frag {
-    static_assert(R * BK % (8 * 256) == 0, "whole 16-byte pieces per thread");
-    uint4 v[R * BK / 8 / 256];
-};
-template <int R>
-__device__ __forceinline__ void load_frag(Frag<R> &f, const uint16_t *P, int64_t s_row, int rows,
-                                          int K, int r0, int k0)
-{
+// ---------------------------------------------------------------------------
+// A block of 32*RB rows through 256-wide layers: four wavefronts, wavefront w
+// owns the output columns 64w .. 64w+63 of every row of the block.  The weight
+// matrices (256 rows of the output column, k contiguous) stream through LDS 64
+// k at a time, double buffered, and kAhead chunks are in flight to registers
+// before that.  The rows' activations come from a 64-wide chunk beside it
+// (first layer) or from the whole hidden tile in LDS.  LDS rows are padded to
+// 72 and 264 entries, so that the 16-byte reads of 32 consecutive rows spread
+// over all banks.
+// The weights are the matrix instruction's first operand, so a lane's four
+// consecutive accumulators are four consecutive output columns of one row and
+// go to the tile with one 8-byte write.
+// ---------------------------------------------------------------------------
+constexpr int BK = 64, LDK = BK + 8, LDT = HID + 8;
+constexpr int kWBuf = HID * LDK;  // entries of one weight chunk
+constexpr int kAhead = 2;         // chunks in flight: chunk c passes slot and buffer c % 2
+
+template <int RB, int WR>
+struct Block {
+    static constexpr int R = 32 * RB * WR, kThreads = 256 * WR;
+    static constexpr int kXBuf = R * LDK;
+    static constexpr int kTile = R * LDT > 2 * kXBuf ? R * LDT : 2 * kXBuf;
+    uint16_t *W;     // two weight chunks
+    uint16_t *tile;  // R x LDT hidden rows; first two X chunks of R x LDK
+    v4u32 wreg[kAhead][8 / WR], xreg[kAhead][RB];
+    v16f32 acc[RB][2];
+
+    // this wavefront's first row
+    __device__ __forceinline__ static int first_row()
+    {
+        return WR == 1 ? 0 : 32 * RB * (int)(threadIdx.x >> 8);
+    }
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-    for (int t = 0; t < R * BK / 8 / 256; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        const int r = e / (BK / 8), kc = (e % (BK / 8)) * 8;
-        const int gr = r0 + r, gk = k0 + kc;
-        const uint16_t *src = P + gr * s_row + gk;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (gr < rows) {
-            if (gk + 8 <= K && ((reinterpret_cast<uintptr_t>(src) & 15) == 0)) {
-                v = *reinterpret_cast<const uint4 *>(src);
-            } else {
-                uint16_t tmp[8];
+        for (int a = 0; a < RB; ++a)
 #pragma unroll
-                for (int q = 0; q < 8; ++q) tmp[q] = (gk + q < K) ? src[q] : (uint16_t)0;
-                v = make_uint4(tmp[0] | (uint32_t)tmp[1] << 16, tmp[2] | (uint32_t)tmp[3] << 16,
-                               tmp[4] | (uint32_t)tmp[5] << 16, tmp[6] | (uint32_t)tmp[7] << 16);
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc[a][b][q] = 0.0f;
+    }
+    // 64 k from w on of the 256 rows of a matrix (row stride K), on their way to
+    // slot q
+    template <bool AL>
+    __device__ __forceinline__ void load_w(const uint16_t *w, int K, int q)
+    {
+#pragma unroll
+        for (int t = 0; t < 8 / WR; ++t)
+            wreg[q][t] =
+                load8<AL>(w + ((threadIdx.x >> 3) + 32 * WR * t) * K + (threadIdx.x & 7) * 8);
+    }
+    __device__ __forceinline__ void store_w(int q, int buf)
+    {
+#pragma unroll
+        for (int t = 0; t < 8 / WR; ++t)
+            *reinterpret_cast<v4u32 *>(W + buf * kWBuf + ((threadIdx.x >> 3) + 32 * WR * t) * LDK +
+                                       (threadIdx.x & 7) * 8) = wreg[q][t];
+    }
+    // multiply one weight chunk with 64 k of the rows at `x` (row stride ldx).
+    // 32x32x16: lane l holds row l%32 of an operand, k = 8*(l/32) + 0..7
+    __device__ __forceinline__ void multiply(int buf, const uint16_t *x, int ldx)
+    {
+        const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+        const uint16_t *wp = W + buf * kWBuf + (64 * wave + (lane & 31)) * LDK + 8 * (lane >> 5);
+        const uint16_t *xp = x + (first_row() + (lane & 31)) * ldx + 8 * (lane >> 5);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 16) {
+            v8bf16 wv[2], xv[RB];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                wv[b] = *reinterpret_cast<const v8bf16 *>(wp + 32 * b * LDK + kk);
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+                xv[a] = *reinterpret_cast<const v8bf16 *>(xp + 32 * a * ldx + kk);
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[b], xv[a], acc[a][b], 0, 0, 0);
+        }
+    }
+    // the product of the tile with w, whose first kAhead chunks are on their
+    // way already; ends at a barrier.  The loops over chunks stay rolled (two
+    // steps, one per slot): straight-line code that runs once waits for its
+    // own instructions.
+    template <bool AL>
+    __device__ __forceinline__ void layer_on_tile(const uint16_t *w)
+    {
+#pragma unroll 1
+        for (int c0 = 0; c0 < HID / BK; c0 += kAhead) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int c = c0 + q;
+                store_w(q, q);
+                if (c + kAhead < HID / BK) load_w<AL>(w + (c + kAhead) * BK, HID, q);
+                __syncthreads();
+                multiply(q, tile + c * BK, LDT);
             }
         }
-        f.v[t] = v;
+        __syncthreads();
     }
-}
-template <int R>
-__device__ __forceinline__ void store_frag(uint16_t (*tile)[LDK], const Frag<R> &f)
-{
-#pragma unroll
-    for (int t = 0; t < R * BK / 8 / 256; ++t) {
-        const int e = threadIdx.x + 256 * t;
-        const int r = e / (BK / 8), kc = (e % (BK / 8)) * 8;
-        *reinterpret_cast<uint4 *>(&tile[r][kc]) = f.v[t];
-    }
-}
-
-__global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
-{
-    // one LDS buffer: the A and B tiles during the products, the output tile
-    // of the forward epilogue afterwards
-    constexpr int kTiles = (BM + BN) * LDK, kOut = BM * (BN + 8);
-    __shared__ __attribute__((aligned(16))) uint16_t smem[kTiles > kOut ? kTiles : kOut];
-    uint16_t (*As)[LDK] = reinterpret_cast<uint16_t (*)[LDK]>(smem);
-    uint16_t (*Bs)[LDK] = reinterpret_cast<uint16_t (*)[LDK]>(smem + BM * LDK);
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wm = (wave >> 1) * WM, wn = (wave & 1) * 64;  // this wave's WM x 64 sub-tile
-    v16f32 acc[AM][2];
-#pragma unroll
-    for (int a = 0; a < AM; ++a)
+    // accumulator register q of lane l: output column 8*(q/4) + 4*(l/32) + q%4
+    // of its 32, row l%32
+    __device__ __forceinline__ void to_tile()
+    {
+        const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) acc[a][b][q] = 0.0f;
-    const int row = lane & 31, kh = 8 * (lane >> 5);
-    // both operands k-contiguous (the forward pass): the next tile's reads
-    // overlap this tile's products
-    const bool piped = g.a_col == 1 && g.b_col == 1;
-    Frag<BM> fa;
-    Frag<BN> fb;
-    if (piped) {
-        load_frag(fa, g.A, g.a_row, g.M, g.K, m0, 0);
-        load_frag(fb, g.B, g.b_row, g.N, g.K, n0, 0);
-    }
-    for (int k0 = 0; k0 < g.K; k0 += BK) {
-        if (piped) {
-            store_frag(As, fa);
-            store_frag(Bs, fb);
-        } else {
-            stage<BM>(As, g.A, g.a_row, g.a_col, g.M, g.K, m0, k0);
-            stage<BN>(Bs, g.B, g.b_row, g.b_col, g.N, g.K, n0, k0);
-        }
-        __syncthreads();
-        if (piped && k0 + BK < g.K) {
-            load_frag(fa, g.A, g.a_row, g.M, g.K, m0, k0 + BK);
-            load_frag(fb, g.B, g.b_row, g.N, g.K, n0, k0 + BK);
-        }
+            for (int g = 0; g < 4; ++g) {
+                const int n = 64 * wave + 32 * b + 8 * g + 4 * (lane >> 5);
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 16) {
-            // 32x32x16: lane l holds A[l%32][8*(l/32) + 0..7] and B[l%32][same k]
-            v8bf16 av[AM], bv[2];
-#pragma unroll
-            for (int a = 0; a < AM; ++a)
-                av[a] = *reinterpret_cast<const v8bf16 *>(&As[wm + 32 * a + row][kk + kh]);
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                bv[b] = *reinterpret_cast<const v8bf16 *>(&Bs[wn + 32 * b + row][kk + kh]);
-#pragma unroll
-            for (int a = 0; a < AM; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // accumulator register q of lane l: row 8*(q/4) + 4*(l/32) + q%4, column l%32
-    if (g.ep == EP_BIAS_RELU_BF16 && m0 + BM <= g.M && n0 + BN <= g.N && (g.N & 7) == 0 &&
-        (reinterpret_cast<uintptr_t>(g.out_bf16) & 15) == 0) {
-        // full tile of the forward pass: bias + ReLU + bf16 into LDS, then
-        // 16-byte row-contiguous stores
-        uint16_t (*Cs)[BN + 8] = reinterpret_cast<uint16_t (*)[BN + 8]>(smem);
-#pragma unroll
-        for (int a = 0; a < AM; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int cl = wn + 32 * b + (lane & 31);
-                const float bias = g.bias[n0 + cl];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const int rl = wm + 32 * a + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-                    const float v = acc[a][b][q] + bias;
-                    Cs[rl][cl] = to_bf16(v > 0.0f ? v : 0.0f);
-                }
+                for (int a = 0; a < RB; ++a)
+                    *reinterpret_cast<uint2 *>(tile + (first_row() + 32 * a + (lane & 31)) * LDT + n) =
+                        make_uint2(pack_bf16(acc[a][b][4 * g], acc[a][b][4 * g + 1]),
+                                   pack_bf16(acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]));
             }
-        __syncthreads();
-        for (int e = threadIdx.x; e < BM * BN / 8; e += 256) {
-            const int r = e / (BN / 8), c = (e % (BN / 8)) * 8;
-            *reinterpret_cast<uint4 *>(g.out_bf16 + (int64_t)(m0 + r) * g.N + n0 + c) =
-                *reinterpret_cast<const uint4 *>(&Cs[r][c]);
+    }
+};
+
+// bias + ReLU + bf16 of the accumulators into the tile
+template <int RB, int WR>
+__device__ __forceinline__ void relu_to_tile(Block<RB, WR> &B, const float *bias)
+{
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+    float bv[2][16];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            bv[b][q] = bias[64 * wave + 32 * b + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3)];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const float v = B.acc[a][b][q] + bv[b][q];
+                B.acc[a][b][q] = v > 0.0f ? v : 0.0f;
+            }
+    B.to_tile();
+}
+
+// the tile's live rows to global memory, 16 bytes a lane
+template <int RB, int WR, bool AL>
+__device__ __forceinline__ void tile_out(const Block<RB, WR> &B, uint16_t *out, int row0, int M)
+{
+#pragma unroll
+    for (int t = 0; t < 4 * RB; ++t) {
+        const int r = (threadIdx.x >> 5) + 8 * WR * t, c = (threadIdx.x & 31) * 8;
+        if (row0 + r < M)
+            store8<AL>(out + (int64_t)(row0 + r) * HID + c,
+                       *reinterpret_cast<const v4u32 *>(B.tile + r * LDT + c));
+    }
+}
+
+// Sums over the wavefront's lanes, in the order of a butterfly over lane
+// distances 32, 16, 8, 4, 2, 1.  The first two steps of four sums share their
+// instructions: a swap of the halves (quarters) of two registers leaves one
+// register of lower and one of upper halves, and one addition serves both.
+__device__ __forceinline__ float swap_add32(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// each lane's sum over its 16 lanes; the partner at distance d is reached by a
+// rotation by d, since the sums so far repeat every 2d lanes
+__device__ __forceinline__ float row_sum(float s)
+{
+#define TSF_ROR_ADD(n)                                                                          \
+    s += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s),      \
+                                                               0x120 + n, 0xF, 0xF, true))
+    TSF_ROR_ADD(8);
+    TSF_ROR_ADD(4);
+    TSF_ROR_ADD(2);
+    TSF_ROR_ADD(1);
+#undef TSF_ROR_ADD
+    return s;
+}
+__device__ __forceinline__ float wave_sum(float s)
+{
+    s = swap_add32(s, s);
+    return row_sum(swap_add16(s, s));
+}
+// the sums of a, c, b and d in lanes 0-15, 16-31, 32-47 and 48-63
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d)
+{
+    return row_sum(swap_add16(swap_add32(a, b), swap_add32(c, d)));
+}
+
+struct FwdArgs {
+    const uint16_t *X, *w1t, *w2t, *w3;
+    const float *b1, *b2, *b3;
+    int M;
+    uint16_t *h1, *h2;  // null: not stored
+    float *logit;
+};
+
+// The forward pass of a block of rows.  Layer 1 reads X (1 KiB a row) and W1
+// once, its output stays in LDS for layer 2, whose output stays there for the
+// logit; h1 and h2 are written where the caller wants them.  32,768 rows move
+// 67 MB, 14.6 us at the 4.6 TB/s of a large copy, and take 19.9 us (12.9 us of
+// it products and LDS traffic alone); as a GEMM per layer and a kernel for the
+// logit they took 38.8 us.  At 4,096 rows the weights through each workgroup
+// bound it: 10.1 us, of which 3.7 us are their reads.
+template <int RB, int WR, bool AL>
+__global__ void __launch_bounds__(256 * WR) fwd_kernel(FwdArgs g)
+{
+    using Bl = Block<RB, WR>;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kWBuf + Bl::kTile];
+    Bl B;
+    B.W = smem;
+    B.tile = smem + 2 * kWBuf;
+    const int row0 = blockIdx.x * Bl::R;
+    // this thread's pieces of an X chunk (rows past the end read the last one)
+    const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 8;
+    const uint16_t *xsrc[RB];
+#pragma unroll
+    for (int t = 0; t < RB; ++t) {
+        const int r = row0 + xr + 32 * WR * t;
+        xsrc[t] = g.X + (int64_t)(r < g.M ? r : g.M - 1) * IN + xc;
+    }
+    const auto load_x = [&](int c, int q) {
+#pragma unroll
+        for (int t = 0; t < RB; ++t) B.xreg[q][t] = load8<AL>(xsrc[t] + c * BK);
+    };
+    constexpr int C1 = IN / BK;
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c) {
+        B.template load_w<AL>(g.w1t + c * BK, IN, c);
+        load_x(c, c);
+    }
+    B.clear();
+#pragma unroll 1
+    for (int c0 = 0; c0 < C1; c0 += kAhead) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int c = c0 + q;
+            uint16_t *xb = B.tile + q * Bl::kXBuf;
+            B.store_w(q, q);
+#pragma unroll
+            for (int t = 0; t < RB; ++t)
+                *reinterpret_cast<v4u32 *>(xb + (xr + 32 * WR * t) * LDK + xc) = B.xreg[q][t];
+            // the chunk two steps on, of W1 or the first ones of W2
+            const int cn = c + kAhead;
+            const bool more = cn < C1;
+            B.template load_w<AL>(more ? g.w1t + cn * BK : g.w2t + (cn - C1) * BK,
+                                  more ? IN : HID, q);
+            if (more) load_x(cn, q);
+            __syncthreads();
+            B.multiply(q, xb, LDK);
+        }
+    }
+    __syncthreads();
+    relu_to_tile<RB, WR>(B, g.b1);
+    __syncthreads();
+    if (g.h1) tile_out<RB, WR, AL>(B, g.h1, row0, g.M);
+    B.clear();
+    B.template layer_on_tile<AL>(g.w2t);
+    relu_to_tile<RB, WR>(B, g.b2);
+    __syncthreads();
+    if (g.h2) tile_out<RB, WR, AL>(B, g.h2, row0, g.M);
+    // logit: lane l sums columns l, l+64, l+128, l+192 of a row
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float w3[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w3[q] = from_bf16(g.w3[lane + 64 * q]);
+    const float b3 = g.b3[0];
+#pragma unroll 2
+    for (int i = 0; i < 2 * RB; ++i) {
+        const int r = wave * 8 * RB + 4 * i;
+        float s[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[e] = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                s[e] += from_bf16(B.tile[(r + e) * LDT + lane + 64 * q]) * w3[q];
+        }
+        const float v = wave_sum4(s[0], s[2], s[1], s[3]);
+        const int out = row0 + r + (lane >> 4);
+        if ((lane & 15) == 0 && out < g.M) g.logit[out] = v + b3;
+    }
+}
+
+// loss derivative of a row with respect to its logit
+__device__ __forceinline__ float logit_delta(float z, float y, int M)
+{
+    const float sig = 1.0f / (1.0f + __expf(-z));
+    return (sig - y) / (float)M;
+}
+
+struct DeltaArgs {
+    const float *logit, *y;
+    const uint16_t *h1, *h2, *w2, *w3;
+    int M;
+    float *d3;
+    uint16_t *d2, *d1;
+};
+
+// delta3 = (sigmoid(logit) - y) / M; delta2 = bf16(delta3 w3 [h2 > 0]);
+// delta1 = bf16((delta2 W2^T) [h1 > 0]) for 32*RB rows; delta2 stays in LDS as
+// the operand of its product.
+template <int RB, int WR, bool AL>
+__global__ void __launch_bounds__(256 * WR) delta_kernel(DeltaArgs g)
+{
+    using Bl = Block<RB, WR>;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kWBuf + Bl::kTile];
+    __shared__ float dz[Bl::R];
+    Bl B;
+    B.W = smem;
+    B.tile = smem + 2 * kWBuf;
+    const int row0 = blockIdx.x * Bl::R;
+#pragma unroll
+    for (int c = 0; c < kAhead; ++c) B.template load_w<AL>(g.w2 + c * BK, HID, c);
+    if (threadIdx.x < Bl::R) {
+        const int r = row0 + threadIdx.x;
+        float d = 0.0f;
+        if (r < g.M) {
+            d = logit_delta(g.logit[r], g.y[r], g.M);
+            g.d3[r] = d;
+        }
+        dz[threadIdx.x] = d;
+    }
+    const int c8 = (threadIdx.x & 31) * 8;
+    float w3[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w3[q] = from_bf16(g.w3[c8 + q]);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 4 * RB; ++t) {
+        const int r = (threadIdx.x >> 5) + 8 * WR * t;
+        v4u32 o = {0, 0, 0, 0};
+        if (row0 + r < g.M) {
+            const v4u32 h = load8<AL>(g.h2 + (int64_t)(row0 + r) * HID + c8);
+            const float d = dz[r];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float lo = from_bf16((uint16_t)h[q]), hi = from_bf16((uint16_t)(h[q] >> 16));
+                o[q] = pack_bf16(lo > 0.0f ? d * w3[2 * q] : 0.0f, hi > 0.0f ? d * w3[2 * q + 1] : 0.0f);
+            }
+            store8<AL>(g.d2 + (int64_t)(row0 + r) * HID + c8, o);
+        }
+        *reinterpret_cast<v4u32 *>(B.tile + r * LDT + c8) = o;
+    }
+    B.clear();
+    // delta1[m][k] = sum_n delta2[m][n] W2[k][n]
+    B.template layer_on_tile<AL>(g.w2);
+    B.to_tile();
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 4 * RB; ++t) {
+        const int r = (threadIdx.x >> 5) + 8 * WR * t;
+        if (row0 + r >= g.M) continue;
+        const v4u32 h = load8<AL>(g.h1 + (int64_t)(row0 + r) * HID + c8);
+        v4u32 d = *reinterpret_cast<const v4u32 *>(B.tile + r * LDT + c8);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!(from_bf16((uint16_t)h[q]) > 0.0f)) d[q] &= 0xFFFF0000u;
+            if (!(from_bf16((uint16_t)(h[q] >> 16)) > 0.0f)) d[q] &= 0x0000FFFFu;
+        }
+        store8<AL>(g.d1 + (int64_t)(row0 + r) * HID + c8, d);
+    }
+}
+
+struct GradArgs {
+    const uint16_t *X, *h1, *h2, *d1, *d2;
+    const float *d3, *logit, *y;
+    int M;
+    float *grad, *loss;
+};
+
+constexpr int kGradWaves = 16;
+typedef short v4s16 __attribute__((ext_vector_type(4)));
+
+// Sum of a value per wavefront of the workgroup, in wavefront order
+__device__ __forceinline__ float block_sum(float v, float *sh)
+{
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kGradWaves; ++w) s += sh[w];
+    return s;
+}
+
+// Every gradient of the network and the loss, sums over the M rows.  A
+// workgroup owns a 32 x 32 tile of dW1^T = delta1^T X or dW2^T = delta2^T h1
+// and its sixteen wavefronts take 32 rows each in turn, so the sum over the
+// rows needs no atomics and no workspace and its order is fixed.  The rows are
+// the contracted dimension, while memory holds them row by row: a wavefront
+// stages 32 rows x 32 columns of both operands in its own LDS and reads them
+// back transposed (ds_read_b64_tr_b16: 16 lanes read four rows of 16 entries
+// and receive a column each).  4,096 rows take 14.7 us, where tiled GEMMs of
+// strided operands over 8 and 16 workgroups took 1.5 ms; the reads bound it
+// (every tile reads 128 bytes of every row).  The column sums db1 and db2 come from a second
+// product with ones in the tiles of the first 32 columns.  dW3 = h2^T delta3
+// (fp32 delta3, so no matrix instruction) takes eight workgroups more, db3 and
+// the loss one.  Blocks go to the XCDs in turn: one XCD's tiles share their
+// columns of X or h1, so its L2 holds an eighth of them.
+template <bool AL>
+__global__ void __launch_bounds__(1024) grad_kernel(GradArgs g)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t stage[kGradWaves][2][32 * 32];
+    __shared__ float sums[kGradWaves][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    if (j == 25) {
+        // db3 and the loss
+        float sd = 0.0f, sl = 0.0f;
+        for (int m = threadIdx.x; m < g.M; m += 64 * kGradWaves) {
+            sd += g.d3[m];
+            const float z = g.logit[m];
+            // softplus(z) - y z, computed stably
+            const float sp = z > 0.0f ? z + log1pf(__expf(-z)) : log1pf(__expf(z));
+            sl += (sp - g.y[m] * z) / (float)g.M;
+        }
+        sd = block_sum(sd, sums[0]);
+        sl = block_sum(sl, sums[0]);
+        if (threadIdx.x == 0) {
+            g.loss[0] = sl;
+            g.grad[O_B3] = sd;
+            g.grad[O_B3 + 1] = g.grad[O_B3 + 2] = g.grad[O_B3 + 3] = 0.0f;
         }
         return;
     }
+    const int pr = lane >> 2, pc = (lane & 3) * 8;  // this lane's piece of 16 rows x 32 columns
+    if (j == 24) {
+        // dW3 of columns 32x .. 32x+31
+        float s[8];
 #pragma unroll
-    for (int a = 0; a < AM; ++a)
+        for (int q = 0; q < 8; ++q) s[q] = 0.0f;
+        for (int m = wave * 16 + pr; m < g.M; m += 16 * kGradWaves) {
+            const v4u32 h = load8<AL>(g.h2 + (int64_t)m * HID + 32 * x + pc);
+            const float d = g.d3[m];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int col = n0 + wn + 32 * b + (lane & 31);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int rr = m0 + wm + 32 * a + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-                if (rr >= g.M || col >= g.N) continue;
-                float v = acc[a][b][q];
-                const int64_t o = (int64_t)rr * g.N + col;
-                if (g.ep == EP_BIAS_RELU_BF16) {
-                    v += g.bias[col];
-                    g.out_bf16[o] = to_bf16(v > 0.0f ? v : 0.0f);
-                } else if (g.ep == EP_MASK_BF16) {
-                    const bool keep = from_bf16(g.mask[o]) > 0.0f;
-                    g.out_bf16[o] = to_bf16(keep ? v : 0.0f);
-                } else {
-                    g.out_f32[o] = v;
-                }
+            for (int q = 0; q < 4; ++q) {
+                s[2 * q] += d * from_bf16((uint16_t)h[q]);
+                s[2 * q + 1] += d * from_bf16((uint16_t)(h[q] >> 16));
             }
         }
-}
-
-// logit = h2 . w3 + b3; one wavefront per row
-__global__ void __launch_bounds__(256) logit_kernel(const uint16_t *h2, const uint16_t *w3,
-                                                    const float *b3, int M, float *logit)
-{
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= M) return;
-    float s = 0.0f;
-    for (int n = lane; n < HID; n += 64)
-        s += from_bf16(h2[(int64_t)row * HID + n]) * from_bf16(w3[n]);
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) logit[row] = s + b3[0];
-}
-
-// delta3 = (sigmoid(logit) - y) / M; delta2 = bf16(delta3 w3 [h2 > 0]); loss
-__global__ void __launch_bounds__(256) delta_kernel(const float *logit, const float *y,
-                                                    const uint16_t *h2, const uint16_t *w3, int M,
-                                                    float *d3, uint16_t *d2, float *loss)
-{
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= M) return;
-    const float z = logit[row];
-    const float sig = 1.0f / (1.0f + __expf(-z));
-    const float dz = (sig - y[row]) / (float)M;
-    if (lane == 0) {
-        d3[row] = dz;
-        // softplus(z) - y z, computed stably
-        const float sp = z > 0.0f ? z + log1pf(__expf(-z)) : log1pf(__expf(z));
-        atomicAdd(loss, (sp - y[row] * z) / (float)M);
-    }
-    for (int n = lane; n < HID; n += 64) {
-        const int64_t o = (int64_t)row * HID + n;
-        const bool keep = from_bf16(h2[o]) > 0.0f;
-        d2[o] = to_bf16(keep ? dz * from_bf16(w3[n]) : 0.0f);
-    }
-}
-
-// column sums: out[n] += sum over this block's rows of A[m][n] (bf16 A), or
-// of w[m] A[m][n] when w is given; out must be zeroed first
-__global__ void __launch_bounds__(256) colsum_kernel(const uint16_t *A, const float *w, int M,
-                                                     int N, float *out)
-{
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    const int m_begin = blockIdx.y * 64, m_end = min(M, m_begin + 64);
-    float s = 0.0f;
-    for (int m = m_begin; m < m_end; ++m) {
-        const float a = from_bf16(A[(int64_t)m * N + n]);
-        s += w ? w[m] * a : a;
-    }
-    atomicAdd(&out[n], s);
-}
-
-__global__ void sum_kernel(const float *v, int M, float *out)
-{
-    __shared__ float sh[256];
-    float s = 0.0f;
-    for (int m = threadIdx.x; m < M; m += 256) s += v[m];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            for (int off = 32; off >= 4; off >>= 1) s[q] += __shfl_xor(s[q], off);
+            if (lane < 4) sums[wave][pc + q] = s[q];
+        }
         __syncthreads();
+        if (threadIdx.x < 32) {
+            float t = 0.0f;
+            for (int w = 0; w < kGradWaves; ++w) t += sums[w][threadIdx.x];
+            g.grad[O_W3 + 32 * x + threadIdx.x] = t;
+        }
+        return;
     }
-    if (threadIdx.x == 0) out[0] = sh[0];
+    const bool first = j < 16;  // dW1^T, else dW2^T
+    const uint16_t *A = first ? g.d1 : g.d2, *Bm = first ? g.X : g.h1;
+    const int K = first ? IN : HID;
+    const int n0 = 32 * (j & 7), k0 = 32 * (first ? (j >> 3) * 8 + x : x);
+    const bool colsum = k0 == 0;
+    v16f32 acc, one;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[q] = one[q] = 0.0f;
+    v8bf16 ones;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ones[q] = (__bf16)1.0f;
+    uint16_t *sa = stage[wave][0], *sb = stage[wave][1];
+    // transposed read: lanes of group l/16 read rows 8*(l/32) + 0..3 (and 4..7)
+    // at columns 16*((l/16)%2) + 0..15
+    const int tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    v4u32 ra[2], rb[2];
+    const uint16_t *pa = A + n0 + pc, *pb = Bm + k0 + pc;
+    const auto load = [&](int m0) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int m = m0 + pr + 16 * t;
+            const int64_t mc = m < g.M ? m : g.M - 1;
+            const uint32_t keep = m < g.M ? ~0u : 0u;  // zeros past the end
+            ra[t] = load8<AL>(pa + mc * HID) & keep;
+            rb[t] = load8<AL>(pb + mc * K) & keep;
+        }
+    };
+    const auto transposed = [&](const uint16_t *s, int step) {
+        typedef __attribute__((address_space(3))) v4s16 lds_v4;
+        const v4s16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(s + tr + 16 * 32 * step));
+        const v4s16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(s + tr + 16 * 32 * step + 4 * 32));
+        return __builtin_bit_cast(v8bf16, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    int m0 = wave * 32;
+    if (m0 < g.M) load(m0);
+    for (; m0 < g.M; m0 += 32 * kGradWaves) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            *reinterpret_cast<v4u32 *>(sa + (pr + 16 * t) * 32 + pc) = ra[t];
+            *reinterpret_cast<v4u32 *>(sb + (pr + 16 * t) * 32 + pc) = rb[t];
+        }
+        if (m0 + 32 * kGradWaves < g.M) load(m0 + 32 * kGradWaves);
+        // the wavefront's own stores are complete before its reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int step = 0; step < 2; ++step) {
+            const v8bf16 av = transposed(sa, step), bv = transposed(sb, step);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
+            if (colsum) one = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, one, 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // the wavefronts' partial tiles, each in its own 4 KiB of `stage`; register
+    // q of lane l: row 8*(q/4) + 4*(l/32) + q%4, column l%32
+    float *part = reinterpret_cast<float *>(&stage[0][0][0]);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
+        part[wave * 1024 + r * 32 + (lane & 31)] = acc[q];
+        if (colsum && (lane & 31) == 0) sums[wave][r] = one[q];
+    }
+    __syncthreads();
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kGradWaves; ++w) s += part[w * 1024 + threadIdx.x];
+    g.grad[(first ? O_W1T : O_W2T) + (n0 + (threadIdx.x >> 5)) * K + k0 + (threadIdx.x & 31)] = s;
+    if (colsum && threadIdx.x < 32) {
+        float t = 0.0f;
+        for (int w = 0; w < kGradWaves; ++w) t += sums[w][threadIdx.x];
+        g.grad[(first ? O_B1 : O_B2) + n0 + threadIdx.x] = t;
+    }
+}
+constexpr int kGradBlocks = 8 * 25 + 1;
+// `stage` holds a wavefront's operands and later its partial tile
+static_assert(2 * 32 * 32 * sizeof(uint16_t) == 32 * 32 * sizeof(float), "stage size");
+
+// bf16 compute copies of parameter i: W1^T, W2^T, W2, w3
+__device__ __forceinline__ void copy_param(int i, float v, uint16_t *q)
+{
+    const uint16_t h = to_bf16(v);
+    if (i < O_B1) {
+        q[Q_W1T + i] = h;
+    } else if (i >= O_W2T && i < O_B2) {
+        const int e = i - O_W2T, n = e / HID, k = e % HID;  // W2[k][n] = W2^T[n][k]
+        q[Q_W2T + e] = h;
+        q[Q_W2 + k * HID + n] = h;
+    } else if (i >= O_W3 && i < O_B3) {
+        q[Q_W3 + i - O_W3] = h;
+    }
 }
 
-__global__ void zero_kernel(float *p, int n)
+// Adam (Kingma & Ba) on the fp32 masters, then their bf16 copies
+__global__ void __launch_bounds__(256) adam_kernel(float *p, const float *g, float *m, float *v,
+                                                   uint16_t *q, float lr, float b1, float b2,
+                                                   float eps, float c1, float c2)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
-}
-
-// Adam (Kingma & Ba) on the fp32 masters
-__global__ void adam_kernel(float *p, const float *g, float *m, float *v, int n, float lr, float b1,
-                            float b2, float eps, float c1, float c2)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
+    if (i >= TSF_MLP_NPARAM) return;
     const float gi = g[i];
     const float mi = b1 * m[i] + (1.0f - b1) * gi;
     const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = pi;
+    copy_param(i, pi, q);
 }
 
-// bf16 compute copies from the fp32 masters: W1^T, W2^T, W2, w3
-__global__ void sync_kernel(const float *p, uint16_t *q)
+__global__ void __launch_bounds__(256) sync_kernel(const float *p, uint16_t *q)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < HID * IN) q[Q_W1T + i] = to_bf16(p[O_W1T + i]);
-    if (i < HID * HID) {
-        q[Q_W2T + i] = to_bf16(p[O_W2T + i]);
-        const int n = i / HID, k = i % HID;  // W2[k][n] = W2^T[n][k]
-        q[Q_W2 + k * HID + n] = to_bf16(p[O_W2T + i]);
-    }
-    if (i < HID) q[Q_W3 + i] = to_bf16(p[O_W3 + i]);
+    if (i < TSF_MLP_NPARAM) copy_param(i, p[i], q);
 }
 
-tsf_status launch_gemm(const GemmArgs &g, hipStream_t s)
-{
-    dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM);
-    if (grid.y > 65535u) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", g.M);
-    hipLaunchKernelGGL(gemm_kernel, grid, dim3(256), 0, s, g);
-    if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "GEMM launch failed");
-    return TSF_OK;
-}
+bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// The rows of a workgroup, by what fills the 256 CUs in one turn: 128 rows
+// (eight wavefronts) above 16,384 rows, 64 above 8,192, 32 below.  The weights,
+// 384 KiB through every workgroup, favour large blocks (32,768 rows: 19.9 us
+// with 128 rows, 26.3 us with 64) until CUs are left idle (16,384 rows: 13.4 us
+// with 64).
+int rows_per_block(int M) { return M > 16384 ? 128 : M > 8192 ? 64 : 32; }
+
+// the largest M that the row blocks of the forward and backward pass accept
+constexpr int kMaxRows = 65535 * 64;
 
 tsf_status check_net(const tsf_mlp *net)
 {
@@ -384,7 +687,7 @@ tsf_status tsf_mlp_sync(const tsf_mlp *net, void *hip_stream)
 {
     tsf_status st = check_net(net);
     if (st) return st;
-    hipLaunchKernelGGL(sync_kernel, dim3((HID * IN + 255) / 256), dim3(256), 0,
+    hipLaunchKernelGGL(sync_kernel, dim3((TSF_MLP_NPARAM + 255) / 256), dim3(256), 0,
                        (hipStream_t)hip_stream, net->param, net->wbf);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "sync launch failed");
     return TSF_OK;
@@ -397,21 +700,17 @@ tsf_status tsf_mlp_fwd(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_
     if (st) return st;
     if (M < 0 || (M > 0 && (!X || !h1 || !h2 || !logit))) return tsf_fail(TSF_E_ARG, "bad forward arguments");
     if (M == 0) return TSF_OK;
-    hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs g;
-    std::memset(&g, 0, sizeof g);
-    g.A = X; g.a_row = IN; g.a_col = 1;
-    g.B = net->wbf + Q_W1T; g.b_row = IN; g.b_col = 1;
-    g.M = M; g.N = HID; g.K = IN;
-    g.ep = EP_BIAS_RELU_BF16; g.bias = net->param + O_B1; g.out_bf16 = h1;
-    if ((st = launch_gemm(g, s))) return st;
-    g.A = h1; g.a_row = HID;
-    g.B = net->wbf + Q_W2T; g.b_row = HID;
-    g.K = HID; g.bias = net->param + O_B2; g.out_bf16 = h2;
-    if ((st = launch_gemm(g, s))) return st;
-    hipLaunchKernelGGL(logit_kernel, dim3((M + 3) / 4), dim3(256), 0, s, h2, net->wbf + Q_W3,
-                       net->param + O_B3, M, logit);
-    if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "logit launch failed");
+    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
+    const FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
+                    net->param + O_B2, net->param + O_B3, M, h1, h2, logit};
+    const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2);
+    const int rows = al ? rows_per_block(M) : 32;
+    auto *fn = !al ? fwd_kernel<1, 1, false> : rows == 128 ? fwd_kernel<2, 2, true>
+                                             : rows == 64 ? fwd_kernel<1, 2, true>
+                                                          : fwd_kernel<1, 1, true>;
+    hipLaunchKernelGGL(fn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0,
+                       (hipStream_t)hip_stream, g);
+    if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "forward launch failed");
     return TSF_OK;
 }
 
@@ -424,41 +723,19 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
     if (!net->grad) return tsf_fail(TSF_E_ARG, "null gradient buffer");
     if (M <= 0 || !X || !y || !h1 || !h2 || !logit || !d2 || !d1 || !d3 || !loss)
         return tsf_fail(TSF_E_ARG, "bad backward arguments");
+    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
     hipStream_t s = (hipStream_t)hip_stream;
-    float *gp = net->grad;
-    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(256), 0, s, loss, 1);
-    hipLaunchKernelGGL(delta_kernel, dim3((M + 3) / 4), dim3(256), 0, s, logit, y, h2,
-                       net->wbf + Q_W3, M, d3, d2, loss);
-    // dW3 = h2^T d3, db3 = sum d3, db2 = colsum d2
-    const dim3 cs_grid(1, (M + 63) / 64);
-    hipLaunchKernelGGL(zero_kernel, dim3((TSF_MLP_NPARAM + 255) / 256), dim3(256), 0, s, gp,
-                       TSF_MLP_NPARAM);
-    hipLaunchKernelGGL(colsum_kernel, cs_grid, dim3(256), 0, s, h2, d3, M, HID, gp + O_W3);
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s, d3, M, gp + O_B3);
-    hipLaunchKernelGGL(colsum_kernel, cs_grid, dim3(256), 0, s, d2, (const float *)nullptr, M, HID,
-                       gp + O_B2);
-    GemmArgs g;
-    std::memset(&g, 0, sizeof g);
-    // dW2^T[n][k] = sum_m d2[m][n] h1[m][k]
-    g.A = d2; g.a_row = 1; g.a_col = HID;
-    g.B = h1; g.b_row = 1; g.b_col = HID;
-    g.M = HID; g.N = HID; g.K = M;
-    g.ep = EP_F32; g.out_f32 = gp + O_W2T;
-    if ((st = launch_gemm(g, s))) return st;
-    // d1 = (d2 W2^T) [h1 > 0]: d1[m][k] = sum_n d2[m][n] W2[k][n]
-    g.A = d2; g.a_row = HID; g.a_col = 1;
-    g.B = net->wbf + Q_W2; g.b_row = HID; g.b_col = 1;
-    g.M = M; g.N = HID; g.K = HID;
-    g.ep = EP_MASK_BF16; g.mask = h1; g.out_bf16 = d1; g.out_f32 = nullptr;
-    if ((st = launch_gemm(g, s))) return st;
-    hipLaunchKernelGGL(colsum_kernel, cs_grid, dim3(256), 0, s, d1, (const float *)nullptr, M, HID,
-                       gp + O_B1);
-    // dW1^T[n][k] = sum_m d1[m][n] X[m][k]
-    g.A = d1; g.a_row = 1; g.a_col = HID;
-    g.B = X; g.b_row = 1; g.b_col = IN;
-    g.M = HID; g.N = IN; g.K = M;
-    g.ep = EP_F32; g.mask = nullptr; g.out_bf16 = nullptr; g.out_f32 = gp + O_W1T;
-    if ((st = launch_gemm(g, s))) return st;
+    const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2) &&
+                    aligned16(d1) && aligned16(d2);
+    const int rows = al ? rows_per_block(M) : 32;
+    const DeltaArgs d{logit, y, h1, h2, net->wbf + Q_W2, net->wbf + Q_W3, M, d3, d2, d1};
+    auto *dfn = !al ? delta_kernel<1, 1, false> : rows == 128 ? delta_kernel<2, 2, true>
+                                                : rows == 64 ? delta_kernel<1, 2, true>
+                                                             : delta_kernel<1, 1, true>;
+    hipLaunchKernelGGL(dfn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0, s, d);
+    const GradArgs g{X, h1, h2, d1, d2, d3, logit, y, M, net->grad, loss};
+    auto *gfn = al ? grad_kernel<true> : grad_kernel<false>;
+    hipLaunchKernelGGL(gfn, dim3(kGradBlocks), dim3(64 * kGradWaves), 0, s, g);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "backward launch failed");
     return TSF_OK;
 }
@@ -473,10 +750,10 @@ tsf_status tsf_mlp_step(const tsf_mlp *net, float lr, float beta1, float beta2, 
     hipStream_t s = (hipStream_t)hip_stream;
     const float c1 = 1.0f - powf(beta1, (float)step), c2 = 1.0f - powf(beta2, (float)step);
     hipLaunchKernelGGL(adam_kernel, dim3((TSF_MLP_NPARAM + 255) / 256), dim3(256), 0, s,
-                       net->param, net->grad, net->adam_m, net->adam_v, TSF_MLP_NPARAM, lr, beta1,
-                       beta2, eps, c1, c2);
+                       net->param, net->grad, net->adam_m, net->adam_v, net->wbf, lr, beta1, beta2,
+                       eps, c1, c2);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "adam launch failed");
-    return tsf_mlp_sync(net, hip_stream);
+    return TSF_OK;
 }
 
 }  // extern "C"
