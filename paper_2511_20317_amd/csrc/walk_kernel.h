@@ -88,32 +88,52 @@ struct KArgs {
 
 constexpr int kLearnRows = 8;  // candidate rows per walk in the learned workspace
 
-// bf16 bit patterns of +1 and -1
-constexpr uint16_t kBf16One = 0x3F80, kBf16MinusOne = 0xBF80;
+// bf16 bit pattern of +1 (-1 has the sign bit too)
+constexpr uint16_t kBf16One = 0x3F80;
 
 // Feature row of the proposal network (512 bf16): six blocks of 64 entries
 // (+1 / -1 / 0 of the factors x_i y_i z_i x_j y_j z_j), the format one-hot at
-// 384 + slot, the rank one-hot at 400 + min(rank, 95), zeros elsewhere.
-__device__ __forceinline__ void write_feature_row(uint16_t *row, const uint64_t (&f)[12], int slot,
-                                                  int rank)
+// 384 + slot, the rank one-hot at 400 + min(rank, 95), zeros elsewhere.  Piece
+// `lane` is entries 8*lane .. 8*lane+7; d and s are the masks of block lane/8
+// (not read from lane 48 on).
+struct FeaturePiece {
+    uint32_t w[4];
+};
+__device__ __forceinline__ FeaturePiece feature_piece(int lane, uint64_t d, uint64_t s, int slot,
+                                                      int rank)
 {
-    uint32_t *w32 = reinterpret_cast<uint32_t *>(row);
-    for (int b = 0; b < 6; ++b) {
-        const uint64_t d = f[2 * b], s = f[2 * b + 1];
-#pragma unroll 4
-        for (int e = 0; e < 64; e += 2) {
-            const uint32_t lo = ((d >> e) & 1) ? (((s >> e) & 1) ? kBf16MinusOne : kBf16One) : 0u;
-            const uint32_t hi =
-                ((d >> (e + 1)) & 1) ? (((s >> (e + 1)) & 1) ? kBf16MinusOne : kBf16One) : 0u;
-            w32[(b * 64 + e) >> 1] = lo | (hi << 16);
-        }
+    uint32_t one, neg;  // entries that are non-zero, and -1 among them
+    if (lane < 48) {
+        const int sh = 8 * (lane & 7);
+        one = (uint32_t)(d >> sh) & 0xFFu;
+        neg = (uint32_t)(s >> sh) & one;
+    } else {
+        const int fs = 384 + slot - 8 * lane;
+        const int rs = 400 + (rank < 95 ? (rank < 0 ? 0 : rank) : 95) - 8 * lane;
+        one = (fs >= 0 && fs < 8 ? 1u << fs : 0u) | (rs >= 0 && rs < 8 ? 1u << rs : 0u);
+        neg = 0;
     }
-    const int fs = 384 + slot;
-    const int rs = 400 + (rank < 95 ? (rank < 0 ? 0 : rank) : 95);
-    for (int e = 384; e < 512; e += 2) {
-        const uint32_t lo = (e == fs || e == rs) ? kBf16One : 0u;
-        const uint32_t hi = (e + 1 == fs || e + 1 == rs) ? kBf16One : 0u;
-        w32[e >> 1] = lo | (hi << 16);
+    FeaturePiece o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t a = (one >> (2 * e)) & 3u, b = (neg >> (2 * e)) & 3u;
+        o.w[e] = (a & 1u) * kBf16One | (a >> 1) * ((uint32_t)kBf16One << 16) | (b & 1u) << 15 |
+                 (b >> 1) << 31;
+    }
+    return o;
+}
+// one 16-byte store where the row allows it
+__device__ __forceinline__ void store_feature_piece(uint16_t *row, int lane, const FeaturePiece &f)
+{
+    uint16_t *p = row + 8 * lane;
+    if ((reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+        *reinterpret_cast<uint4 *>(p) = make_uint4(f.w[0], f.w[1], f.w[2], f.w[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            p[2 * e] = (uint16_t)f.w[e];
+            p[2 * e + 1] = (uint16_t)(f.w[e] >> 16);
+        }
     }
 }
 
@@ -1707,7 +1727,12 @@ struct Walker {
                     f[2 * q] = (uint64_t)fv[q].d;
                     f[2 * q + 1] = (uint64_t)fv[q].s;
                 }
-                write_feature_row(a->feat + ((size_t)walk * kLearnRows + gl) * 512, f, fmt_slot, r);
+                uint16_t *row = a->feat + ((size_t)walk * kLearnRows + gl) * 512;
+#pragma unroll 1
+                for (int e = 0; e < 64; ++e) {
+                    const int b = e < 48 ? e >> 3 : 0;
+                    store_feature_piece(row, e, feature_piece(e, f[2 * b], f[2 * b + 1], fmt_slot, r));
+                }
             }
         }
         if (gl < kLearnRows) a->cand[(size_t)walk * kLearnRows + gl] = desc;
