@@ -29,7 +29,8 @@
 //    per LDS read), then the validity of the two roles for the few matches;
 //  * term-parallel (TP, any size): attempts run one after another and the G
 //    lanes split the terms (slot q of lane l is term q*G + l), with one group
-//    ballot per slot and role;
+//    ballot per slot and role; with one walk per wavefront the lanes compare
+//    fingerprints of their terms held in registers (section FP);
 //  * indexed attempt-parallel (IX, at most 64 terms): AP over a match index
 //    kept in LDS after the terms of the workgroup -- for every term k and
 //    factor kind X a 64-bit mask of the other live terms whose factor X
@@ -266,6 +267,15 @@ struct Walker {
     static_assert(!AP || S == 1 || (S == 2 && !IX), "attempt-parallel partner sets of 1 or 2 words");
     static constexpr int NW = AP ? S : 1;
     using PSet = TermSet<NW>;
+    // one walk per wavefront, term-parallel: every factor of a lane's terms has
+    // a fingerprint in a register (see the section FP below)
+    static constexpr bool kFP = !AP && G == 64;
+    uint32_t fp[kFP ? S : 1][3];
+    bool fp_stale;  // the fingerprints do not describe the terms in LDS
+    // kFP: pb holds the blocks of several iterations, 2^dsh lanes each (attempts
+    // from the first lane on, the gates in the last); dbase: the first lane of
+    // the current iteration, 64 before the next draw
+    int dsh, dbase;
     // group geometry
     int gl;      // lane within the group
     int gshift;  // first lane of the group within the wavefront
@@ -316,12 +326,11 @@ struct Walker {
         else
             return (m >> gshift) & ((1ull << G) - 1);
     }
-    // `lane` is the same in every lane of the group; the term-parallel kernels
-    // with register slot copies (one group per wavefront) read it with a
-    // scalar readlane instead of a lane permute
+    // `lane` is the same in every lane of the group; with one group per
+    // wavefront it is read with a scalar readlane instead of a lane permute
     __device__ __forceinline__ uint32_t from_lane(uint32_t v, int lane) const
     {
-        if constexpr (G == 64 && kRegSlots)
+        if constexpr (kFP)
             return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
         else
             return (uint32_t)__shfl((int)v, gshift + lane);
@@ -334,9 +343,13 @@ struct Walker {
     // absorbs) instead of occupying twenty registers for the whole kernel.
     __device__ __forceinline__ Philox4 draw(uint32_t att, uint32_t dom) const
     {
+        return draw_at((uint64_t)t, att, dom);
+    }
+    __device__ __forceinline__ Philox4 draw_at(uint64_t tt, uint32_t att, uint32_t dom) const
+    {
         uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
         asm volatile("" : "+v"(k0), "+v"(k1));
-        return philox4x32_10((uint32_t)(uint64_t)t, (uint32_t)((uint64_t)t >> 32), att, dom, k0, k1);
+        return philox4x32_10((uint32_t)tt, (uint32_t)(tt >> 32), att, dom, k0, k1);
     }
 
     __device__ __forceinline__ int idx(int k, int X) const { return (X * cap2 + k) * kFW; }
@@ -357,9 +370,11 @@ struct Walker {
         if constexpr (PK) return unpack(q[0]);
         return TV<T>{q[0], q[1]};
     }
+    // (one walk per wavefront: every lane stores the same word, so that no lane
+    // test makes the values around it look divergent to the compiler)
     __device__ __forceinline__ void st(int k, int X, TV<T> v)
     {
-        if (gl == 0) {
+        if (kFP || gl == 0) {
             T *q = lds + idx(k, X);
             if constexpr (PK) {
                 q[0] = pack(v);
@@ -570,6 +585,7 @@ struct Walker {
         const int last = r - 1;
         if (tr0 == h) tr0 = -1;
         if (tr1 == h) tr1 = -1;
+        fp_stale = true;
         if constexpr (IX) {
             // drop bit h from every mask; bit `last` becomes bit h, and the
             // masks of term `last` move to slot h
@@ -593,6 +609,10 @@ struct Walker {
                 if (h != last) lds[idx(h, gl)] = lds[idx(last, gl)];
                 lds[idx(last, gl)] = kDead;
             }
+        } else if constexpr (kFP) {
+            // lanes past the sixth repeat its move
+            const int q = gl < 5 ? gl : 5;
+            lds[idx(h, q >> 1) + (q & 1)] = lds[idx(last, q >> 1) + (q & 1)];
         } else if (h != last) {
             for (int q = gl; q < 3 * kFW; q += G) {
                 const int X = q / kFW, w = q % kFW;
@@ -744,6 +764,10 @@ struct Walker {
         }
         st(i, Y, ny);
         st(j, Z, nz);
+        if constexpr (kFP) {
+            set_fp(i, Y, fhash(ny, Y));
+            set_fp(j, Z, fhash(nz, Z));
+        }
         wave_lds_sync();
     }
 
@@ -764,15 +788,269 @@ struct Walker {
         }
     }
 
+    // ------------------------------------------------------------------ FP
+    // The term-parallel kernels with one walk per wavefront compare
+    // fingerprints instead of factors: a 32-bit hash of a factor's masks (w in
+    // the sign that makes its first entry positive, since w is compared up to
+    // sign), odd for live terms and 0 for dead slots, held in registers for the
+    // S terms of the lane.  Finding the terms that share a factor with term i
+    // is then one comparison per slot against a scalar; only the lanes with a
+    // match read that term from LDS and compare exactly.  A flip changes two fingerprints; after a removal, merge, expand
+    // or restart they are all taken anew from LDS before their next use.
+    // Comparing the factors themselves took four words each, from LDS or from
+    // register copies of every slot.  8,192 (6,7,9) walks x 1,000 iterations:
+    // 20.7 -> 15.7 ms; a round of 16,384 exploratory walks (64-bit factors, 128
+    // terms) 11.9 -> 8.5 ms; 1,777 (3,4,5) walks in this shape 5.1 -> 2.4 us an
+    // iteration.  What bounds it is the wavefront's own instruction stream
+    // (LDS holds two wavefronts per SIMD at (6,7,9)), so every value that is
+    // the same in all lanes is kept scalar.
+    __device__ __forceinline__ static uint32_t fhash(TV<T> v, int X)
+    {
+        T sg = v.s;
+        if (!Z2 && X == 2 && (v.s & v.d & (~v.d + 1))) sg ^= v.d;
+        uint32_t h = (uint32_t)v.d * 0x9E3779B1u;
+        if constexpr (sizeof(T) == 8) h += (uint32_t)((uint64_t)v.d >> 32) * 0x85EBCA77u;
+        if constexpr (!Z2) {
+            h += (uint32_t)sg * 0xC2B2AE3Du;
+            if constexpr (sizeof(T) == 8) h += (uint32_t)((uint64_t)sg >> 32) * 0x27D4EB2Fu;
+        }
+        return (h + (uint32_t)X * 0x165667B2u) | 1u;  // (kinds told apart)
+    }
+    __device__ void refresh_fp()
+    {
+        if (!fp_stale) return;
+        fp_stale = false;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int k = q * 64 + gl;
+            TV<T> f[3];
+            load_term(k < cap2 ? k : cap2 - 1, f);
+#pragma unroll
+            for (int X = 0; X < 3; ++X) fp[q][X] = k < r ? fhash(f[X], X) : 0u;
+        }
+    }
+    // One code path per kind, ended by an assembly comment of its own: were the
+    // ends alike, the compiler would merge them into accesses through a
+    // computed address and keep the fingerprints in scratch memory.
+    template <int X>
+    __device__ __forceinline__ static void keep_apart()
+    {
+        asm volatile("; kind %0" ::"n"(X));
+    }
+    // fingerprint of factor X of term k := h
+    template <int X>
+    __device__ __forceinline__ void set_fp_x(int k, uint32_t h)
+    {
+#pragma unroll
+        for (int q = 0; q < S; ++q) fp[q][X] = q * 64 + gl == k ? h : fp[q][X];
+        keep_apart<X>();
+    }
+    __device__ __forceinline__ void set_fp(int k, int X, uint32_t h)
+    {
+        if (X == 0)
+            set_fp_x<0>(k, h);
+        else if (X == 1)
+            set_fp_x<1>(k, h);
+        else
+            set_fp_x<2>(k, h);
+    }
+    // this lane's slots (bit q) whose factor X has fingerprint h, without term
+    // self.  With one or two slots all three kinds are compared: a hash that
+    // agrees with another kind's is dropped by the exact comparison, and three
+    // comparisons cost less than branching on the kind.
+    template <int X>
+    __device__ __forceinline__ uint32_t match_fp_x(uint32_t h) const
+    {
+        uint32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < S; ++q) c |= fp[q][X] == h ? 1u << q : 0u;
+        return c;
+    }
+    __device__ __forceinline__ uint32_t drop_term(uint32_t c, int k) const
+    {
+        return gl == (k & 63) ? c & ~(1u << (k >> 6)) : c;
+    }
+    __device__ __forceinline__ uint32_t match_fp(uint32_t h, int X, int self) const
+    {
+        uint32_t c = 0;
+        if constexpr (S <= 2) {
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                c |= ((fp[q][0] == h) | (fp[q][1] == h) | (fp[q][2] == h)) ? 1u << q : 0u;
+        } else if (X == 0) {
+            c = match_fp_x<0>(h);
+            keep_apart<0>();
+        } else if (X == 1) {
+            c = match_fp_x<1>(h);
+            keep_apart<1>();
+        } else {
+            c = match_fp_x<2>(h);
+            keep_apart<2>();
+        }
+        return drop_term(c, self);
+    }
+    // Candidate partners of (i, X) whose factor X has fingerprint h: this
+    // lane's slots that are valid in role 0 and 1 (c0, c1); returns whether the
+    // wavefront has any.  A round tests one matching slot of every lane, so
+    // the few partners that a factor has take one round as a rule.
+    __device__ bool candidates_fp(int i, int X, uint32_t h, uint32_t &c0, uint32_t &c1) const
+    {
+        c0 = c1 = 0;
+        uint32_t c = match_fp(h, X, i);
+        if (!__ballot(c != 0)) return false;
+        const int A = X == 0 ? 1 : 0, B = X == 2 ? 1 : 2;
+        const TV<T> xi = ld(i, X), Ai = ld(i, A), Bi = ld(i, B);
+        do {
+            if (c != 0) {
+                const int q = S == 1 ? 0 : __builtin_ctz(c);
+                const int k = q * 64 + gl;
+                const TV<T> xk = ld(k, X), Ak = ld(k, A), Bk = ld(k, B);
+                const int sg = rel(xi, xk, X);  // 0: the fingerprints agree, the factors do not
+                TV<T> o1, o2;
+                const bool a1 = axpy(sg, Ai, Ak, o1), b1 = axpy(-1, Bk, Bi, o2);
+                const bool a2 = axpy(sg, Bi, Bk, o1), b2 = axpy(-1, Ak, Ai, o2);
+                const bool keep = sg != 0 && (!additions || (Ai.d != Ak.d && Bi.d != Bk.d));
+                c0 |= (a1 && b1 && keep) ? 1u << q : 0u;
+                c1 |= (a2 && b2 && keep) ? 1u << q : 0u;
+                c &= c - 1;
+            }
+        } while (S > 1 && __ballot(c != 0));
+        return __ballot((c0 | c1) != 0) != 0;
+    }
+    // An attempt (or a pair of the cyclic search) per lane: its term, kind and
+    // the fingerprint of that factor
+    struct Probe {
+        int i, X;
+        uint32_t h;
+    };
+    __device__ __forceinline__ Probe probe(int i, int X) const
+    {
+        return Probe{i, X, fhash(ld(i, X), X)};
+    }
+    // the candidates of the probe in `lane`
+    __device__ __forceinline__ bool try_probe(const Probe &p, int lane, uint32_t &c0,
+                                              uint32_t &c1) const
+    {
+        return candidates_fp((int)from_lane((uint32_t)p.i, lane),
+                             (int)from_lane((uint32_t)p.X, lane), from_lane(p.h, lane), c0, c1);
+    }
+    __device__ __forceinline__ uint32_t pick_probe(const Probe &p, int lane, uint32_t word,
+                                                   uint32_t c0, uint32_t c1) const
+    {
+        return pick_fp((int)from_lane((uint32_t)p.i, lane), (int)from_lane((uint32_t)p.X, lane),
+                       word, c0, c1);
+    }
+    // candidate `word` of the partners of (i, X), role 0 then 1, j ascending
+    __device__ __forceinline__ uint32_t pick_fp(int i, int X, uint32_t word, uint32_t c0,
+                                                uint32_t c1) const
+    {
+        uint64_t m0[S], m1[S];
+        int n0 = 0, n1 = 0;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            m0[q] = __ballot((c0 >> q) & 1u);
+            m1[q] = __ballot((c1 >> q) & 1u);
+            n0 += popc64(m0[q]);
+            n1 += popc64(m1[q]);
+        }
+        int c = (int)below(word, (uint32_t)(n0 + n1));
+        const int role = c >= n0;
+        if (role) c -= n0;
+#pragma unroll
+        for (int q = 0; q < S; ++q) m0[q] = role ? m1[q] : m0[q];
+        return pack_flip(i, select_tp(m0, c), X, role);
+    }
+    // the searches of choose_flip and fallback_tp: the lanes read the factors
+    // of up to 64 attempts (pairs of the cyclic search) at once, then the
+    // attempts are tried in order
+    __device__ uint32_t choose_flip_fp()
+    {
+        refresh_fp();
+        const int T_ = a->flip_tries;
+        uint32_t c0, c1;
+        {
+            const Probe p = probe((int)below(pb.x[0], (uint32_t)r), (int)below(pb.x[1], 3u));
+            const int nb = T_ < G - 1 ? T_ : G - 1;  // attempt 63 is drawn below
+            for (int e = 0; e < nb; ++e)
+                if (try_probe(p, dbase + e, c0, c1)) {
+                    cnt[C_ATTEMPTS] += (uint32_t)(e + 1);
+                    return pick_probe(p, dbase + e, from_lane(pb.x[2], dbase + e), c0, c1);
+                }
+        }
+        cnt[C_ATTEMPTS] += (uint32_t)T_;
+        if (T_ == G) {
+            const Philox4 w = draw((uint32_t)(G - 1), 0);
+            const Probe p = probe((int)below(w.x[0], (uint32_t)r), (int)below(w.x[1], 3u));
+            if (try_probe(p, 0, c0, c1)) return pick_probe(p, 0, from_lane(w.x[2], 0), c0, c1);
+        }
+        cnt[C_FALLBACKS]++;
+        const uint32_t f0 = from_lane(pb.x[3], dbase), f1 = from_lane(pb.x[3], dbase + 1);
+        const int npairs = 3 * r;
+        const int p0 = (int)below(f0, (uint32_t)npairs);
+        for (int base = 0; base < npairs; base += G) {
+            int pq = p0 + base + gl;
+            if (pq >= npairs) pq -= npairs;
+            if (pq >= npairs) pq = 0;  // lanes past the last pair
+            const Probe p = probe(pq / 3, pq % 3);
+            const int nb = npairs - base < G ? npairs - base : G;
+            for (int e = 0; e < nb; ++e)
+                if (try_probe(p, e, c0, c1)) return pick_probe(p, e, f1, c0, c1);
+        }
+        return kNoFlip;
+    }
+    // First term k (ascending) that merges with term ia (ib), -1 where there is
+    // none or the tracked index is -1: the terms sharing two fingerprints are
+    // found by comparisons, and only those are read.
+    __device__ void find_merges_fp(int ia, int ib, int &ka, int &kb)
+    {
+        refresh_fp();
+        // lanes 0..2: the factors of term ia, lanes 3..5: of term ib
+        const int X = gl % 3, t = gl < 3 ? ia : ib;
+        const uint32_t h = fhash(ld(t < 0 ? 0 : t, X), X);
+        const uint32_t ca = ia < 0 ? 0u : two_shared_fp(h, 0, ia);
+        const uint32_t cb = ib < 0 ? 0u : two_shared_fp(h, 3, ib);
+        ka = kb = -1;
+        if (!__ballot((ca | cb) != 0)) return;  // the common case
+        ka = first_merge_fp(ia, ca);
+        kb = first_merge_fp(ib, cb);
+    }
+    // this lane's slots that agree in two or three of the fingerprints of lanes
+    // l, l+1, l+2 of h, without term self
+    __device__ __forceinline__ uint32_t two_shared_fp(uint32_t h, int l, int self) const
+    {
+        const uint32_t u = match_fp_x<0>(from_lane(h, l)), v = match_fp_x<1>(from_lane(h, l + 1)),
+                       w = match_fp_x<2>(from_lane(h, l + 2));
+        return drop_term((u & v) | (u & w) | (v & w), self);
+    }
+    __device__ int first_merge_fp(int ti, uint32_t c) const
+    {
+        if (ti < 0) return -1;
+        TV<T> tt[3];
+        load_term(ti, tt);
+        int found = -1;
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            for (uint64_t m = found < 0 ? __ballot((c >> q) & 1u) : 0ull; m; m &= m - 1) {
+                const int k = q * 64 + __builtin_ctzll(m);
+                TV<T> tk[3], o;
+                load_term(k, tk);
+                if (merge_kind(tt, tk, o) >= 0) {
+                    found = k;
+                    break;
+                }
+            }
+        return found;
+    }
+
     // ------------------------------------------------------------------ TP
-    // With four to seven slots per lane the three factors of this lane's S
+    // With four slots per lane the three factors of this lane's S
     // terms (k = q*G + lane, indexes clamped to the rows) are read in one
     // round: the attempts and the cyclic search of an iteration compare
     // against these registers, since no term changes before a flip is
     // chosen.  With fewer slots each attempt reads the factors it compares
     // (measured faster there); eight slots of copies would not fit in 256
     // VGPRs.
-    static constexpr bool kRegSlots = !AP && S >= 4 && S <= 7;
+    static constexpr bool kRegSlots = !AP && !kFP && S == 4;
     __device__ __forceinline__ void load_slots(TV<T> (&F)[S][3]) const
     {
         if constexpr (!kRegSlots) return;
@@ -1096,7 +1374,9 @@ struct Walker {
     __device__ uint32_t choose_flip()
     {
         const int T_ = a->flip_tries;
-        if constexpr (AP) {
+        if constexpr (kFP) {
+            return choose_flip_fp();
+        } else if constexpr (AP) {
             update_scan_end();
             constexpr int P = G - 1;  // attempts per batch
             for (int base = 0; base < T_; base += P) {
@@ -1380,11 +1660,15 @@ struct Walker {
         for (;;) {
             const int ia = done0 ? -1 : tr0, ib = tr1;
             if (ia < 0 && ib < 0) break;
-            TV<T> ta[3] = {}, tb[3] = {};
-            if (ia >= 0) load_term(ia, ta);
-            if (ib >= 0) load_term(ib, tb);
             int ka, kb;
-            find_merges(ia, ta, ib, tb, ka, kb);
+            if constexpr (kFP) {
+                find_merges_fp(ia, ib, ka, kb);
+            } else {
+                TV<T> ta[3] = {}, tb[3] = {};
+                if (ia >= 0) load_term(ia, ta);
+                if (ib >= 0) load_term(ib, tb);
+                find_merges(ia, ta, ib, tb, ka, kb);
+            }
             // the first tracked term merges while it has a partner, then the
             // second (one merge_into call site)
             int qq = -1, k = -1;
@@ -1414,7 +1698,10 @@ struct Walker {
     {
         if (r >= r_cap || r < 2) return false;
         for (int att = 0; att < 8; ++att) {
-            const Philox4 w = draw((uint32_t)att, 2);
+            Philox4 w = draw((uint32_t)att, 2);
+            if constexpr (kFP)  // scalars, so that what follows is uniform
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w.x[q] = from_lane(w.x[q], 0);
             const int i = (int)below(w.x[0], (uint32_t)r);
             int j = (int)below(w.x[1], (uint32_t)(r - 1));
             if (j >= i) ++j;
@@ -1447,6 +1734,7 @@ struct Walker {
                 st(i, X, xj);
             }
             wave_lds_sync();
+            fp_stale = true;
             r = nw + 1;
             normalise(i);
             normalise(j);
@@ -1473,6 +1761,7 @@ struct Walker {
     // l of the group moves terms l, l+G, ...
     __device__ void load_scheme(const uint64_t *src, int rr)
     {
+        fp_stale = true;
         for (int k = gl; k < rr; k += G)
 #pragma unroll
             for (int X = 0; X < 3; ++X) {
@@ -1523,7 +1812,7 @@ struct Walker {
     {
 #pragma unroll
         for (int off = G / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, G);
-        return c;
+        return kFP ? __builtin_amdgcn_readfirstlane(c) : c;
     }
     // the stop rule: best rank (additions objective: best naive additions,
     // non-zero coefficients - 2r - mp, Sec. 4.5) at most the target
@@ -1549,11 +1838,24 @@ struct Walker {
 
     __device__ void begin_iteration()
     {
-        // this iteration's draws: lane q < G-1 -> flip attempt q, lane G-1 -> gates
-        const bool gate_lane = gl == G - 1;
-        pb = draw(gate_lane ? 0u : (uint32_t)gl, gate_lane ? 1u : 0u);
+        int gate_from = G - 1;
+        if constexpr (kFP) {
+            // one draw serves 64 >> dsh iterations: the blocks depend on the
+            // iteration number alone, and an iteration needs few of the lanes
+            if (dbase == 64) {
+                const uint32_t att = (uint32_t)gl & ((1u << dsh) - 1u);
+                const bool gates = att == (1u << dsh) - 1u;
+                pb = draw_at((uint64_t)t + (uint64_t)(gl >> dsh), gates ? 0u : att, gates ? 1u : 0u);
+                dbase = 0;
+            }
+            gate_from = dbase + (1 << dsh) - 1;
+        } else {
+            // this iteration's draws: lane q < G-1 -> flip attempt q, lane G-1 -> gates
+            const bool gate_lane = gl == G - 1;
+            pb = draw(gate_lane ? 0u : (uint32_t)gl, gate_lane ? 1u : 0u);
+        }
 #pragma unroll
-        for (int q = 0; q < 3; ++q) gate[q] = from_lane(pb.x[q], G - 1);
+        for (int q = 0; q < 3; ++q) gate[q] = from_lane(pb.x[q], gate_from);
         logging = a->log != nullptr && t <= a->log_cap;
     }
 
@@ -1646,7 +1948,7 @@ struct Walker {
     // (and none in Z2) and no entry beyond the factor's length
     // (TSF_CHECK_CODING); u and v of every live term normalised, Sec. 3.6
     // (TSF_CHECK_NORMALISED); IX: every mask equal to the relation it
-    // indexes (TSF_CHECK_INDEX); PK: slots at or above the rank dead
+    // indexes, FP: every fingerprint that of its factor (TSF_CHECK_INDEX); PK: slots at or above the rank dead
     // (TSF_CHECK_DEAD_SLOTS).  Returns the OR of the failed checks.
     __device__ uint32_t check_state(const int (&len)[3]) const
     {
@@ -1676,6 +1978,18 @@ struct Walker {
                 for (int X = 0; X < 3; ++X)
                     if (lds[idx(k, X)] != kDead) bad |= TSF_CHECK_DEAD_SLOTS;
         }
+        if constexpr (kFP) {
+            if (!fp_stale)
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int k = q * 64 + gl;
+                    TV<T> f[3];
+                    load_term(k < cap2 ? k : cap2 - 1, f);
+#pragma unroll
+                    for (int X = 0; X < 3; ++X)
+                        if (fp[q][X] != (k < rr ? fhash(f[X], X) : 0u)) bad |= TSF_CHECK_INDEX;
+                }
+        }
         uint32_t all = 0;
 #pragma unroll
         for (int b = 0; b < 8; ++b)
@@ -1688,6 +2002,7 @@ struct Walker {
         begin_iteration();
         int fi = -1, fj = -1;
         const bool found = try_flip(fi, fj);
+        if constexpr (kFP) dbase += 1 << dsh;
         finish_iteration(found, fi, fj);
     }
 
@@ -1811,20 +2126,27 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / G;
     const int wpb = blockDim.x >> 6;
-    const int64_t walk = ((int64_t)blockIdx.x * wpb + wave) * W + grp;
+    // one walk per wavefront: the walk's scalars are scalar registers
+    const auto uni = [](int v) { return G == 64 ? __builtin_amdgcn_readfirstlane(v) : v; };
+    const int64_t walk = ((int64_t)blockIdx.x * wpb + uni(wave)) * W + uni(grp);
     if (walk >= a.n_walks) return;  // the whole group leaves together
 
     using Wk = Walker<G, S, T, Z2, AP, IX, PK, CHK>;
     Wk wk;
     wk.gl = lane % G;
-    wk.gshift = grp * G;
+    wk.gshift = uni(grp * G);
+    wk.fp_stale = true;
+    // lanes per iteration's draws: the attempts (two at least, for the cyclic
+    // search's words) and the gates, as a power of two
+    wk.dbase = 64;
+    wk.dsh = a.flip_tries < 4 ? 2 : a.flip_tries < 32 ? 32 - __builtin_clz(a.flip_tries) : 6;
     wk.cap2 = a.cap2;
     wk.capm = a.capm;
     // the terms of every walk of the workgroup (6*cap2 words each), then for
     // IX the masks of every walk (3*capm u64 each); the masks are not padded
     // like the term rows, which keeps a wavefront's LDS small enough for one
     // more wavefront per CU at (3,3,3)
-    const int slot = wave * W + grp;
+    const int slot = uni(wave * W + grp);
     wk.lds = smem + (size_t)slot * a.cap2 * 3 * Wk::kFW;
     wk.mk = reinterpret_cast<uint64_t *>(smem + (size_t)wpb * W * a.cap2 * 3 * Wk::kFW) +
             (size_t)slot * a.capm * 3;
@@ -1940,13 +2262,12 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
 // are held to 128 VGPRs, four wavefronts per SIMD, which their LDS also
 // allows at (3,3,3) (10,176 bytes per 8-walk wavefront, sixteen per CU); the
 // other indexed kernels with 32-bit masks to 168 VGPRs (three per SIMD, as
-// many as their LDS allows); the term-parallel kernels with 64 lanes and four
-// slots per walk (capacities 193-256, e.g. (4,5,12)) also to 168 VGPRs, three
-// per SIMD, which their LDS allows; the rest are not constrained.
+// many as their LDS allows); the rest are not constrained (the term-parallel
+// kernels with 64 lanes need 74 to 130).
 template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK = false>
 __global__ void __launch_bounds__(256) __attribute__((
-    amdgpu_waves_per_eu(PK && G >= 8 ? 4 : (IX && G >= 8 && sizeof(T) == 4) ? 3 :
-                        (!AP && G == 64 && S == 4) ? 3 : 1))) walk_kernel(KArgs a)
+    amdgpu_waves_per_eu(PK && G >= 8 ? 4 : (IX && G >= 8 && sizeof(T) == 4) ? 3 : 1)))
+walk_kernel(KArgs a)
 {
     walk_body<G, S, T, Z2, AP, IX, PK, false>(a);
 }
