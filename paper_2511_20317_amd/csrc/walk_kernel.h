@@ -291,8 +291,22 @@ struct Walker {
     bool additions;
     int nnz, best_nnz, mp;
     int64_t t, plateau_start;
+    int64_t restart_at;  // plateau_start + plateau, or never
+    int64_t log_until;   // last iteration of the training log, 0 without one
+    bool hit;            // the stop rule holds
     uint32_t cnt[C_NUM];
     const KArgs *a;
+    // the arguments (the kernel's only one, so at the start of its argument
+    // segment) for code that seldom runs: read from memory there, where the
+    // compiler would otherwise keep them all in scalar registers for the whole
+    // kernel and spill those into lanes of vector registers
+    __device__ __forceinline__ static const KArgs &rare()
+    {
+        typedef const __attribute__((address_space(4))) KArgs *Const;
+        Const p = (Const)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return *(const KArgs *)p;
+    }
     int64_t walk;
     // this iteration's Philox block of this lane (attempt gl, or the gate)
     Philox4 pb;
@@ -701,7 +715,8 @@ struct Walker {
             sg = rel(xi, xj, X);
         }
         if (logging && gl == 0) {
-            tsf_flip_log *lg = a->log + (size_t)walk * a->log_cap + (t - 1);
+            const KArgs &ra = rare();
+            tsf_flip_log *lg = ra.log + (size_t)walk * ra.log_cap + (t - 1);
             const TV<T> fv[6] = {xi, yi, zi0, xj, yj, zj0};
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
@@ -1823,17 +1838,28 @@ struct Walker {
 
     __device__ void restart_check()
     {
-        if (a->plateau > 0 && t - plateau_start >= a->plateau) {
-            const bool from_best = a->restart_from_best != 0;
-            const uint64_t *src = (from_best ? (const uint64_t *)a->best : a->start) +
-                                  (size_t)walk * a->cap * 6;
+        if (t >= restart_at) {
+            const KArgs &ra = rare();
+            const bool from_best = ra.restart_from_best != 0;
+            const uint64_t *src = (from_best ? (const uint64_t *)ra.best : ra.start) +
+                                  (size_t)walk * ra.cap * 6;
             const int rr = from_best ? best_rank : start_rank;
             load_scheme(src, rr);
             r = rr;
             if (additions) nnz = count_nnz();
-            plateau_start = t;
+            start_plateau();
             cnt[C_RESTARTS]++;
         }
+    }
+    __device__ __forceinline__ void start_plateau()
+    {
+        plateau_start = t;
+        set_restart();
+    }
+    __device__ __forceinline__ void set_restart()
+    {
+        const int64_t pl = rare().plateau, never = INT64_MAX;
+        restart_at = pl <= 0 || pl > never - plateau_start ? never : plateau_start + pl;
     }
 
     __device__ void begin_iteration()
@@ -1856,7 +1882,7 @@ struct Walker {
         }
 #pragma unroll
         for (int q = 0; q < 3; ++q) gate[q] = from_lane(pb.x[q], gate_from);
-        logging = a->log != nullptr && t <= a->log_cap;
+        logging = t <= log_until;
     }
 
     // everything of Algorithm 1 after try_flip
@@ -1896,22 +1922,24 @@ struct Walker {
                 accepted = !improved && r == best_rank && (uint64_t)g0 < a->t_eq;
             }
             if (improved || accepted) {
-                const int c = store_scheme(a->best + (size_t)walk * a->cap * 6);
+                const KArgs &ra = rare();
+                const int c = store_scheme(ra.best + (size_t)walk * ra.cap * 6);
                 best_nnz = additions ? nnz : c;
                 best_rank = r;
+                cnt[C_IMPROVEMENTS] += improved ? 1u : 0u;
+                cnt[C_EQ_ACCEPTS] += improved ? 0u : 1u;
             }
             if (improved) {
-                plateau_start = t;
-                if (gl == 0 && n_rec < a->rec_cap) {
-                    tsf_record *rc = a->rec + (size_t)walk * a->rec_cap + n_rec;
+                start_plateau();
+                hit = reached();
+                const KArgs &ra = rare();
+                if (gl == 0 && n_rec < ra.rec_cap) {
+                    tsf_record *rc = ra.rec + (size_t)walk * ra.rec_cap + n_rec;
                     rc->iter = t;
                     rc->rank = additions ? nnz - 2 * r - mp : r;
                     rc->reserved = 0;
                 }
                 n_rec++;
-                cnt[C_IMPROVEMENTS]++;
-            } else if (accepted) {
-                cnt[C_EQ_ACCEPTS]++;
             }
             if (!additions) {
                 const uint32_t g1 = gate[1];
@@ -1928,7 +1956,8 @@ struct Walker {
     __device__ void write_log(bool flipped)
     {
         if (logging && gl == 0) {
-            tsf_flip_log *lg = a->log + (size_t)walk * a->log_cap + (t - 1);
+            const KArgs &ra = rare();
+            tsf_flip_log *lg = ra.log + (size_t)walk * ra.log_cap + (t - 1);
             lg->iter = t;
             if (!flipped) {
                 lg->rank_before = -1;
@@ -2178,14 +2207,17 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     wk.best_rank = h->best_rank;
     wk.best_nnz = h->best_nnz;
     wk.mp = m * p;
+    wk.target = h->target_rank;
     wk.additions = a.objective == TSF_OBJ_ADDITIONS;
     wk.nnz = 0;
     wk.start_rank = h->start_rank;
-    wk.target = h->target_rank;
     wk.n_rec = h->n_rec;
     wk.t = h->t;
-    const int64_t t_first = wk.t;
+    const uint32_t t_first = (uint32_t)wk.t;
     wk.plateau_start = h->plateau_start;
+    wk.set_restart();
+    wk.log_until = a.log != nullptr ? a.log_cap : 0;
+    wk.hit = wk.reached();
 #pragma unroll
     for (int c = 0; c < C_NUM; ++c) wk.cnt[c] = 0;
     wk.logging = false;
@@ -2222,9 +2254,11 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
             if constexpr (AP && !IX) wk.apply_learned();
         }
     } else {
-        for (int64_t it = 0; it < a.n_iters; ++it) {
-            if (wk.reached()) done = 1;
-            if (done || wk.t >= a.max_iters) break;
+        // the call's last iteration, within the walk's budget
+        const int64_t t_end = a.n_iters < a.max_iters - wk.t ? wk.t + a.n_iters : a.max_iters;
+        // (the counter is the same in every walk, so it is a scalar: setting the
+        // priority must not depend on lanes)
+        for (int64_t it = 0; !wk.hit && wk.t < t_end; ++it) {
             if ((it & 63) == 0) progress_priority(it, a.n_iters);
             wk.t += 1;
             wk.iteration();
@@ -2240,8 +2274,10 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     }
     if ((!CHK || done != -4) && wk.reached()) done = 1;
 
-    wk.store_scheme(a.cur + (size_t)walk * a.cap * 6);
+    const KArgs &ra = wk.rare();
+    wk.store_scheme(ra.cur + (size_t)walk * ra.cap * 6);
     if (wk.gl == 0) {
+        h = ra.hdr + walk;
         h->rank = wk.r;
         h->best_rank = wk.best_rank;
         h->best_nnz = wk.best_nnz;
@@ -2249,10 +2285,10 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
         h->n_rec = wk.n_rec;
         h->t = wk.t;
         h->plateau_start = wk.plateau_start;
-        h->params_hash = a.params_hash;
+        h->params_hash = ra.params_hash;
         if (CHK && done == -4) h->reserved = err;
         // every iteration of this call is a flip or a dead end
-        wk.cnt[C_ITERS] = (uint32_t)(wk.t - t_first);
+        wk.cnt[C_ITERS] = (uint32_t)wk.t - t_first;
         wk.cnt[C_FLIPS] = wk.cnt[C_ITERS] - wk.cnt[C_DEAD_ENDS];
         for (int c = 0; c < C_NUM; ++c) h->counters[c] += wk.cnt[c];
     }
