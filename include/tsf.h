@@ -324,10 +324,14 @@ typedef struct {
  * lanes_per_walk: 4, 8, 16, 32 or 64 (16, 8, 4, 2 or 1 walks per 64-lane
  * wavefront; 4 to 32 for the attempt-parallel strategies, 8 to 64 for the
  * term-parallel one).  waves_per_block: 1..4.  A zero field lets the library
- * choose (a launch chosen by tsf_autotune for batches of this shape, else
- * strategy 3 with 8 lanes up to capacity 64, strategy 1 with 8 lanes up to
- * capacity 128 when max_len <= 32, strategy 2 with 64 lanes otherwise; one
- * wavefront per workgroup).
+ * choose: with all three zero a launch chosen by tsf_autotune for batches of
+ * this shape, if there is one; with strategy and lanes_per_walk zero by
+ * capacity, max_len and n_walks -- strategy 3 up to capacity 64 (32 lanes for
+ * the smallest batches, 16 or 8 for larger ones), strategy 2 with 64 lanes for
+ * small batches and large capacities, strategy 1 with 16 or 8 lanes for large
+ * batches of up to 96 terms; with one of the two given, strategy 3 up to
+ * capacity 64, 1 up to capacity 128 when max_len <= 32, 2 otherwise, and 8
+ * lanes (64 for strategy 2); one wavefront per workgroup.
  * Results never depend on it. */
 typedef struct {
     int32_t lanes_per_walk;
@@ -398,11 +402,11 @@ tsf_status tsf_walk(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_walk_bat
  * header gets done = -4 and reserved = (t << 8) | the failed bits, and its
  * state is written back as it was at that point (not at all when the
  * loaded state failed).  Walks that pass every check end bit-identical to
- * tsf_walk with the same arguments.  Kernels exist for the library's
- * default launch shapes (strategy 0, 8 lanes per walk for the
- * attempt-parallel strategies, 64 for the term-parallel one, one
- * wavefront per workgroup); `launch` may be NULL or name one of them, else
- * TSF_E_ARG.  Slower than tsf_walk (the index check is quadratic in the
+ * tsf_walk with the same arguments.  Kernels exist for one launch shape per
+ * strategy (strategy 0: 3 up to capacity 64, 1 up to capacity 128 when
+ * max_len <= 32, else 2; 8 lanes per walk for the attempt-parallel
+ * strategies, 64 for the term-parallel one, one wavefront per workgroup);
+ * `launch` may be NULL or name one of them, else TSF_E_ARG.  Slower than tsf_walk (the index check is quadratic in the
  * rank).  Errors as tsf_walk. */
 #define TSF_CHECK_RANK 1u
 #define TSF_CHECK_ZERO_FACTOR 2u

@@ -813,6 +813,39 @@ struct Launch {
     bool ap, ix;
 };
 
+// The strategy and lanes per walk of a call that names neither.  Times are us
+// per iteration of the whole batch, rank objective, ternary.
+//  * Small batches do not fill the 1,024 SIMDs, and an iteration's latency
+//    counts: the fewer walks share a wavefront, the less each waits for the
+//    others' branches.  Up to 4,096 walks 32 lanes each ((3,3,3), 1,024 walks:
+//    2.2 with 32 lanes, 2.5 with 8), up to 8,192 walks 16 lanes (capacity 58:
+//    3.2 against 3.8); one wavefront per walk with fingerprints where the
+//    indexed kernels' masks are long (capacity 58, 1,024 walks: 2.3 against 2.6
+//    with 32 lanes).
+//  * Beyond 64 terms the indexed kernels end and the attempts of the
+//    attempt-parallel ones scan every term: one wavefront per walk is faster
+//    until the chip is full (capacity 88: 4,096 walks 3.2 against 8.2 with 8
+//    lanes, 8,192 walks 6.1 against 8.6, 16,384 walks 10.5 against 9.3), and
+//    always above 96 terms, where their partner scans and LDS grow (capacity
+//    108, 65,536 walks: 42 against 54).
+//  * Full chips: 8 lanes, or 16 where a walk's LDS leaves a CU too few
+//    wavefronts of eight walks (capacity 56, 65,536 walks: 14.3 against 15.0;
+//    capacity 88: 30.1 against 32.3; capacity 44: 13.4 against 11.4).
+tsf_launch default_launch(const tsf_walk_params *prm, const tsf_walk_batch *b)
+{
+    const bool wide = b->max_len > 32;
+    const int cap = b->capacity, n = b->n_walks;
+    if (cap <= 64) {
+        if (!wide && cap > 40 && n <= 1024) return tsf_launch{64, 0, 2};
+        const int lanes = n <= 4096 ? 32 : n <= 8192 || wide || cap > 48 ? 16 : 8;
+        return tsf_launch{lanes, 0, 3};
+    }
+    if (wide || cap > 96 || n <= 8192) return tsf_launch{64, 0, 2};
+    const bool sixteen =
+        n <= 16384 || (prm->objective == TSF_OBJ_RANK && (cap > 72 || n <= 40960));
+    return tsf_launch{sixteen ? 16 : 8, 0, 1};
+}
+
 // validate a walk call and build its kernel arguments and launch shape
 tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int64_t n_iters,
                         const tsf_launch *launch, KArgs &a, Launch &L, bool checked = false)
@@ -830,12 +863,15 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
     if (b->log && b->log_cap < 0) return tsf_fail(TSF_E_ARG, "log_cap < 0");
     int strategy = launch ? launch->strategy : 0;
     if (strategy < 0 || strategy > 3) return tsf_fail(TSF_E_ARG, "strategy %d not in 0..3", strategy);
-    // default: the indexed strategy up to 64 terms; the plain attempt-parallel
-    // one up to 128 terms of 32-bit factors; the term-parallel one beyond and
-    // for 64-bit factors (measured on the exploratory workload, capacity 128:
-    // its LDS per walk keeps the attempt-parallel kernels at few wavefronts
-    // per CU once the schemes grow)
     const bool wide = b->max_len > 32;
+    int g = launch ? launch->lanes_per_walk : 0;
+    if (strategy == 0 && g == 0 && !checked) {
+        const tsf_launch d = default_launch(prm, b);
+        strategy = d.strategy;
+        g = d.lanes_per_walk;
+    }
+    // lanes without a strategy, and the checked kernels: the indexed strategy up
+    // to 64 terms, the attempt-parallel one up to 128 terms of 32-bit factors
     if (strategy == 0) strategy = b->capacity <= 64 ? 3 : (b->capacity <= 128 && !wide ? 1 : 2);
     const bool ap = strategy == 1 || strategy == 3;
     const bool ix = strategy == 3;
@@ -843,7 +879,7 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
         return tsf_fail(TSF_E_CAPACITY, "the indexed strategy needs capacity <= 64");
     if (ap && b->capacity > 128)
         return tsf_fail(TSF_E_CAPACITY, "the attempt-parallel strategy needs capacity <= 128");
-    int g = launch && launch->lanes_per_walk ? launch->lanes_per_walk : (ap ? 8 : 64);
+    if (g == 0) g = ap ? 8 : 64;
     int wpb = launch && launch->waves_per_block ? launch->waves_per_block : 1;
     if (g != 4 && g != 8 && g != 16 && g != 32 && g != 64)
         return tsf_fail(TSF_E_ARG, "lanes_per_walk %d not in {4,8,16,32,64}", g);
