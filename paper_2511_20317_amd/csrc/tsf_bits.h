@@ -184,3 +184,78 @@ TSF_HD int factor_rank(uint64_t d, uint64_t s, int rows, int cols, bool z2, int3
     }
     return rank;
 }
+
+// The same rank by elimination on the masks of the whole matrix at once: for a
+// pivot at (row, column), the pivot row times the column's set of rows (one
+// bit at each row's start) is a multiple of the pivot row in each of them, so
+// one step clears the column.  Over GF(2) digits are XORed; over GF(3) p and n
+// are the masks of +1 and -1.
+//
+// Over Q: a minor of a {-1,0,1} matrix of order 2 is at most 2 in size and one
+// of order 3 at most 4, so a non-zero one of order 2 is non-zero modulo 3 and
+// one of order 3 non-zero modulo 2 or 3.  Hence rank <= 1 is exact from GF(3),
+// and the larger of the two ranks is exact up to 2 and wherever it reaches the
+// number of rows or columns with entries; the rest (order 4 and beyond with
+// minors divisible by 6) is left to the caller (-1).
+TSF_HD int mask_rank_gf2(uint64_t d, int cols, uint64_t starts, uint32_t magic)
+{
+    const uint64_t row = (1ull << cols) - 1;
+    int rank = 0;
+    while (d) {
+        const int b = __builtin_ctzll(d);
+        const int r = (int)((uint32_t)b * magic >> 16), c = b - r * cols;  // b / cols, b % cols
+        const uint64_t pivot = (d >> (r * cols)) & row;
+        d ^= ((d >> c) & starts) * pivot;  // clears the pivot row and the column
+        ++rank;
+    }
+    return rank;
+}
+TSF_HD int mask_rank_gf3(uint64_t p, uint64_t n, int cols, uint64_t starts, uint32_t magic)
+{
+    const uint64_t row = (1ull << cols) - 1;
+    int rank = 0;
+    while (p | n) {
+        const int b = __builtin_ctzll(p | n);
+        const int r = (int)((uint32_t)b * magic >> 16), c = b - r * cols;
+        uint64_t pp = (p >> (r * cols)) & row, pn = (n >> (r * cols)) & row;
+        if ((pn >> c) & 1) {
+            const uint64_t x = pp;
+            pp = pn;
+            pn = x;
+        }
+        const uint64_t rp = (p >> c) & starts, rn = (n >> c) & starts;
+        // subtract the pivot row from the rows with +1, add it to those with -1
+        const uint64_t ap = rp * pn + rn * pp, an = rp * pp + rn * pn;
+        const uint64_t z = p | n, a = ap | an;
+        const uint64_t p2 = (p & ~a) | (ap & ~z) | (n & an);
+        n = (n & ~a) | (an & ~z) | (p & ap);
+        p = p2;
+        ++rank;
+    }
+    return rank;
+}
+// rank of a rows x cols factor (at most 64 entries), or -1 (see above); starts:
+// bit r*cols for every row r; magic: 65536 / cols rounded up.  A single column
+// of 64 entries and a single row are ranks of one.
+TSF_HD int factor_rank_masks(uint64_t d, uint64_t s, int rows, int cols, bool z2, uint64_t starts,
+                             uint32_t magic)
+{
+    if (rows == 1 || cols == 1) return d != 0;
+    if (z2) return mask_rank_gf2(d, cols, starts, magic);
+    const int r3 = mask_rank_gf3(d & ~s, s, cols, starts, magic);
+    if (r3 <= 1) return r3;
+    // rows and columns with entries
+    const uint64_t row = (1ull << cols) - 1;
+    uint64_t left = 0;
+    int nr = 0;
+    for (int r = 0; r < rows; ++r) {
+        const uint64_t x = (d >> (r * cols)) & row;
+        left |= x;
+        nr += x != 0;
+    }
+    const int nc = __builtin_popcountll(left), most = nr < nc ? nr : nc;
+    if (r3 == most) return r3;
+    const int r2 = mask_rank_gf2(d, cols, starts, magic);
+    const int best = r2 > r3 ? r2 : r3;
+    return best <= 2 || best == most ? best : -1;
+}

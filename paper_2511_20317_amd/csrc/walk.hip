@@ -20,13 +20,17 @@ namespace {
 using namespace tsfk;
 
 // One wavefront per walk: validate the start scheme, then cur := best :=
-// start and clear the walk's state.
-__global__ void __launch_bounds__(64) init_kernel(tsf_walk_header *hdr, uint64_t *cur,
-                                                  uint64_t *best, const uint64_t *start,
-                                                  int32_t n_walks, int32_t cap)
+// start and clear the walk's state.  A factor's two masks are 16 bytes, so a
+// lane moves factors lane, lane+64, ... of the scheme with one load and two
+// stores each, all coalesced.  16,384 exploratory walks 83 -> 34 us, 65,536
+// walks of the mixed formats 374 -> 147 us (576 MB, 3.9 TB/s); a term per lane,
+// whose 8-byte accesses lay 48 bytes apart, wasted most of each access.
+__global__ void __launch_bounds__(256) init_kernel(tsf_walk_header *hdr, uint64_t *cur,
+                                                   uint64_t *best, const uint64_t *start,
+                                                   int32_t n_walks, int32_t cap)
 {
-    const int64_t walk = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int64_t walk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     if (walk >= n_walks) return;
     tsf_walk_header *h = hdr + walk;
     const int m = h->m, n = h->n, p = h->p, r0 = h->start_rank;
@@ -36,27 +40,37 @@ __global__ void __launch_bounds__(64) init_kernel(tsf_walk_header *hdr, uint64_t
     const int len[3] = {m * n, n * p, p * m};
     ok = ok && len[0] <= 64 && len[1] <= 64 && len[2] <= 64;
     const size_t base = (size_t)walk * cap * 6;
+    // 16-byte accesses where the buffers allow them
+    const bool al = ((reinterpret_cast<uintptr_t>(start) | reinterpret_cast<uintptr_t>(cur) |
+                      reinterpret_cast<uintptr_t>(best)) & 15) == 0;
     bool bad = false;
+    int nnz = 0;  // non-zero coefficients of the start scheme
     if (ok) {
-        for (int k = lane; k < r0; k += 64) {
-            for (int X = 0; X < 3; ++X) {
-                const uint64_t d = start[base + k * 6 + 2 * X], s = start[base + k * 6 + 2 * X + 1];
-                const uint64_t lim = len[X] == 64 ? ~0ull : ((1ull << len[X]) - 1);
-                if (d == 0 || (s & ~d) || (d & ~lim) || (z2 && s)) bad = true;
-                if (!z2 && X < 2 && (s & (d & (~d + 1)))) bad = true;  // not normalised
+        int X = lane % 3;
+        for (int q = lane; q < 3 * r0; q += 64) {
+            ulonglong2 v;
+            const size_t o = base + 2 * (size_t)q;
+            if (al)
+                v = *reinterpret_cast<const ulonglong2 *>(start + o);
+            else
+                v = make_ulonglong2(start[o], start[o + 1]);
+            const uint64_t d = v.x, s = v.y;
+            const int L = X == 0 ? len[0] : X == 1 ? len[1] : len[2];
+            const uint64_t lim = L == 64 ? ~0ull : ((1ull << L) - 1);
+            if (d == 0 || (s & ~d) || (d & ~lim) || (z2 && s)) bad = true;
+            if (!z2 && X < 2 && (s & (d & (~d + 1)))) bad = true;  // not normalised
+            nnz += __builtin_popcountll(d);
+            if (al) {
+                *reinterpret_cast<ulonglong2 *>(cur + o) = v;
+                *reinterpret_cast<ulonglong2 *>(best + o) = v;
+            } else {
+                cur[o] = best[o] = d;
+                cur[o + 1] = best[o + 1] = s;
             }
-            for (int x = 0; x < 6; ++x) {
-                cur[base + k * 6 + x] = start[base + k * 6 + x];
-                best[base + k * 6 + x] = start[base + k * 6 + x];
-            }
+            X = X == 2 ? 0 : X + 1;  // 64 mod 3 = 1
         }
     }
     const bool any_bad = __ballot(bad) != 0;
-    // non-zero coefficients of the start scheme
-    int nnz = 0;
-    if (ok)
-        for (int k = lane; k < r0; k += 64)
-            for (int X = 0; X < 3; ++X) nnz += __builtin_popcountll(start[base + k * 6 + 2 * X]);
     for (int off = 32; off > 0; off >>= 1) nnz += __shfl_xor(nnz, off);
     if (lane == 0) {
         h->done = (!ok || any_bad) ? -2 : 0;
@@ -72,21 +86,103 @@ __global__ void __launch_bounds__(64) init_kernel(tsf_walk_header *hdr, uint64_t
     }
 }
 
-// Brent verification (Eq. 1, C^T form of Sec. 3.1) of one scheme per
-// workgroup: the tensor sum_l u_l (x) v_l (x) w_l is built one u-entry slice
-// at a time in LDS (int32 atomics over the non-zero products), then compared
-// with the matrix multiplication tensor.  A mask bit that encodes no
-// coefficient (a digit at or beyond the factor's length, a sign without its
-// digit, any sign of a Z2 scheme) counts as one violation of its own and
-// takes no part in the tensor.
+// Brent verification (Eq. 1, C^T form of Sec. 3.1), a wavefront per scheme.
+// A lane owns an (a, b) pair of entries of u and v and adds up the row
+// sum_l u_l[a] v_l[b] w_l of the tensor for all entries of w at once, in
+// bit-sliced two's complement: plane k holds bit k of every entry's sum.  The
+// terms of a pair are the intersection of two sets: for every entry of u and v
+// the terms that have it, and those that have it negative, are 64-bit words
+// built with ballots.  So the work is the number of non-zero u_l[a] v_l[b]; the
+// carry steps of a pair's terms bound it.  65,536 schemes of the mixed formats
+// take 256 us; building the tensor with LDS atomics, an atomic for every
+// non-zero product and two barriers for every entry of u, took 1,292 us.  Ten planes hold the sums of up to
+// 512 terms modulo 1,024.  A mask bit that encodes no coefficient (a digit at
+// or beyond the factor's length, a sign without its digit, any sign of a Z2
+// scheme) counts as one violation of its own and takes no part in the tensor.
+// The digits and signs of w take 32-bit words where w has at most 32 entries.
+constexpr int kPlanes = 10;
+// LDS of a wavefront, per 64 terms: w's masks and the four sets of 64 entries
+constexpr size_t kVerifyLds = 64 * 16 + 4 * 64 * 8;
+
+// adds +1 to the entries of `up` and -1 to those of `down`, from plane Z on;
+// carries and borrows run on while there are any (in Z2 only plane 0 counts)
+template <typename T, int Z>
+__device__ __forceinline__ void add_planes(T (&plane)[kPlanes], T up, T down, bool z2)
+{
+    const T x = plane[Z];
+    plane[Z] = x ^ (up | down);
+    if constexpr (Z + 1 < kPlanes) {
+        up &= x;
+        down &= ~x;
+        if (!z2 && (up | down) != 0) add_planes<T, Z + 1>(plane, up, down, z2);
+    }
+}
+
+// violations in the rows of this lane's pairs (a, b)
+template <typename T>
+__device__ __forceinline__ int verify_pairs(const T *W, const uint64_t *Ud, const uint64_t *Us,
+                                            const uint64_t *Vd, const uint64_t *Vs, int all,
+                                            int words, int m, int n, int p, bool z2)
+{
+    const int Lv = n * p, pairs = m * n * Lv;
+    int bad = 0;
+    for (int pair = threadIdx.x & 63; pair < pairs; pair += 64) {
+        const int a = pair / Lv, b = pair - a * Lv;
+        T plane[kPlanes];
+#pragma unroll
+        for (int k = 0; k < kPlanes; ++k) plane[k] = 0;
+        for (int k = 0; k < words; ++k) {
+            uint64_t terms = Ud[a * all + k] & Vd[b * all + k];
+            const uint64_t neg = Us[a * all + k] ^ Vs[b * all + k];
+            for (; terms; terms &= terms - 1) {
+                const int e = __builtin_ctzll(terms), l = 64 * k + e;
+                const T d = W[2 * l];
+                // digits of -1 and +1 of this term
+                const T sg = W[2 * l + 1] ^ ((neg >> e) & 1 ? d : (T)0);
+                add_planes<T, 0>(plane, d & ~sg, sg, z2);
+            }
+        }
+        const int a1 = a / n, a2 = a - a1 * n, b1 = b / p, b2 = b - b1 * p;
+        T diff = plane[0] ^ (a2 == b1 ? (T)1 << (b2 * m + a1) : (T)0);
+#pragma unroll
+        for (int k = 1; k < kPlanes; ++k) diff |= plane[k];
+        bad += __builtin_popcountll((uint64_t)diff);
+    }
+    return bad;
+}
+
+// per entry e of a factor the lanes' terms that have it (D) and have it
+// negative (S): entry e's words go to lane e, which writes them
+__device__ __forceinline__ void entry_sets(uint64_t d, uint64_t s, int L, uint64_t *D, uint64_t *S,
+                                           int all)
+{
+    const int lane = threadIdx.x & 63;
+    uint64_t wd = 0, ws = 0;
+    for (int half = 0; half < 2; ++half) {
+        const uint32_t hd = (uint32_t)(d >> (32 * half)), hs = (uint32_t)(s >> (32 * half));
+        const int end = L - 32 * half < 32 ? L - 32 * half : 32;
+        for (int e = 0; e < end; ++e) {
+            const uint64_t bd = __ballot((hd & (1u << e)) != 0), bs = __ballot((hs & (1u << e)) != 0);
+            const bool mine = lane == 32 * half + e;
+            wd = mine ? bd : wd;
+            ws = mine ? bs : ws;
+        }
+    }
+    if (lane < L) {
+        D[lane * all] = wd;
+        S[lane * all] = ws;
+    }
+}
+
 __global__ void __launch_bounds__(256) verify_kernel(const tsf_walk_header *hdr,
                                                      const uint64_t *schemes, int32_t cap,
                                                      int32_t n_walks, int32_t which,
                                                      int64_t *n_violated)
 {
-    __shared__ int32_t slice[64 * 64];
-    __shared__ int32_t bad_sh;
-    const int64_t q = blockIdx.x;
+    extern __shared__ __attribute__((aligned(16))) unsigned char verify_smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
     if (q >= n_walks) return;
     const tsf_walk_header *h = hdr + q;
     const int m = h->m, n = h->n, p = h->p;
@@ -94,51 +190,49 @@ __global__ void __launch_bounds__(256) verify_kernel(const tsf_walk_header *hdr,
     const bool z2 = h->mode == 1;
     const int Lu = m * n, Lv = n * p, Lw = p * m;
     if (m < 1 || n < 1 || p < 1 || Lu > 64 || Lv > 64 || Lw > 64 || rank < 0 || rank > cap) {
-        if (threadIdx.x == 0) n_violated[q] = -1;
+        if (lane == 0) n_violated[q] = -1;
         return;
     }
+    const int words = (rank + 63) / 64, all = (cap + 63) / 64;
+    unsigned char *mem = verify_smem + (size_t)wave * all * kVerifyLds;
+    uint64_t *Ud = reinterpret_cast<uint64_t *>(mem + (size_t)all * 64 * 16);
+    uint64_t *Us = Ud + 64 * all, *Vd = Us + 64 * all, *Vs = Vd + 64 * all;
+    uint64_t *W64 = reinterpret_cast<uint64_t *>(mem);  // (digits, signs) of w per term
+    uint32_t *W32 = reinterpret_cast<uint32_t *>(mem);
     const uint64_t *sc = schemes + (size_t)q * cap * 6;
-    if (threadIdx.x == 0) bad_sh = 0;
-    int32_t bad = 0;
-    const uint64_t lim[3] = {Lu == 64 ? ~0ull : (1ull << Lu) - 1, Lv == 64 ? ~0ull : (1ull << Lv) - 1,
-                             Lw == 64 ? ~0ull : (1ull << Lw) - 1};
-    for (int l = threadIdx.x; l < rank; l += blockDim.x)
+    const auto mask = [](int L) { return L == 64 ? ~0ull : (1ull << L) - 1; };
+    const uint64_t lims[3] = {mask(Lu), mask(Lv), mask(Lw)};
+    const bool narrow = Lw <= 32;
+    int bad = 0;
+    for (int k = 0; k < words; ++k) {
+        const int l = 64 * k + lane;
+        uint64_t f[6] = {0, 0, 0, 0, 0, 0};
+        if (l < rank)
+#pragma unroll
+            for (int x = 0; x < 6; ++x) f[x] = sc[(size_t)l * 6 + x];
+#pragma unroll
         for (int X = 0; X < 3; ++X) {
-            const uint64_t d = sc[l * 6 + 2 * X], sg = sc[l * 6 + 2 * X + 1];
-            bad += __builtin_popcountll(d & ~lim[X]) +
-                   __builtin_popcountll(z2 ? sg : (sg & ~(d & lim[X])));
+            const uint64_t d = f[2 * X] & lims[X], s = f[2 * X + 1];
+            bad += __builtin_popcountll(f[2 * X] & ~lims[X]) +
+                   __builtin_popcountll(z2 ? s : (s & ~d));
+            f[2 * X] = d;
+            f[2 * X + 1] = z2 ? 0 : s & d;
         }
-    for (int av = 0; av < Lu; ++av) {
-        for (int e = threadIdx.x; e < Lv * Lw; e += blockDim.x) slice[e] = 0;
-        __syncthreads();
-        const int a1 = av / n, a2 = av % n;
-        for (int l = threadIdx.x; l < rank; l += blockDim.x) {
-            const uint64_t ud = sc[l * 6 + 0], us = sc[l * 6 + 1];
-            if (!((ud >> av) & 1)) continue;
-            const int su = ((us >> av) & 1) ? -1 : 1;
-            for (uint64_t dv = sc[l * 6 + 2] & lim[1]; dv; dv &= dv - 1) {
-                const int b = __builtin_ctzll(dv);
-                const int sv = ((sc[l * 6 + 3] >> b) & 1) ? -su : su;
-                for (uint64_t dw = sc[l * 6 + 4] & lim[2]; dw; dw &= dw - 1) {
-                    const int c = __builtin_ctzll(dw);
-                    atomicAdd(&slice[b * Lw + c], ((sc[l * 6 + 5] >> c) & 1) ? -sv : sv);
-                }
-            }
+        if (narrow) {
+            W32[2 * l] = (uint32_t)f[4];
+            W32[2 * l + 1] = (uint32_t)f[5];
+        } else {
+            W64[2 * l] = f[4];
+            W64[2 * l + 1] = f[5];
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < Lv * Lw; e += blockDim.x) {
-            const int b = e / Lw, c = e % Lw;
-            const int b1 = b / p, b2 = b % p, c1 = c / m, c2 = c % m;
-            const int want = (a2 == b1 && b2 == c1 && c2 == a1) ? 1 : 0;
-            int got = slice[e];
-            if (z2) got &= 1;
-            bad += got != want;
-        }
-        __syncthreads();
+        entry_sets(f[0], f[1], Lu, Ud + k, Us + k, all);
+        entry_sets(f[2], f[3], Lv, Vd + k, Vs + k, all);
     }
-    atomicAdd(&bad_sh, bad);
-    __syncthreads();
-    if (threadIdx.x == 0) n_violated[q] = bad_sh;
+    wave_lds_sync();
+    bad += narrow ? verify_pairs<uint32_t>(W32, Ud, Us, Vd, Vs, all, words, m, n, p, z2)
+                  : verify_pairs<uint64_t>(W64, Ud, Us, Vd, Vs, all, words, m, n, p, z2);
+    for (int off = 32; off > 0; off >>= 1) bad += __shfl_xor(bad, off);
+    if (lane == 0) n_violated[q] = bad;
 }
 
 // (r, c) of a row-major rows x cols factor -> the new position, or -1 when
@@ -271,16 +365,23 @@ __global__ void __launch_bounds__(256) features_kernel(const tsf_flip_log *log, 
 }
 
 // Isotropy invariants (Sec. 3.7) of one scheme per wavefront: lane l takes
-// terms l, l+64, ...; the rank of each factor comes from elimination in the
-// lane's own 64-word slice of LDS (factor_rank, shared with the host).
-__global__ void __launch_bounds__(64) invariants_kernel(const tsf_walk_header *hdr,
-                                                       const uint64_t *schemes, int32_t cap,
-                                                       int32_t n_walks, int32_t which,
-                                                       uint8_t *term_ranks, int32_t *rank_sums)
+// factors l, l+64, ... of the scheme (a factor's two masks are one 16-byte
+// load).  The rank comes from elimination on the masks (factor_rank_masks);
+// where that leaves it open, from elimination modulo 65521 on the entries, which
+// every factor took before, in 16 KiB of LDS a wavefront.  65,536 schemes of
+// the mixed formats 998 -> 201 us.
+__device__ int factor_rank_entries(uint64_t d, uint64_t s, int rows, int cols)
 {
-    __shared__ int32_t scratch[64 * 64];
-    const int64_t walk = blockIdx.x;
-    const int lane = threadIdx.x;
+    int32_t M[64];
+    return factor_rank(d, s, rows, cols, false, M);
+}
+__global__ void __launch_bounds__(256) invariants_kernel(const tsf_walk_header *hdr,
+                                                        const uint64_t *schemes, int32_t cap,
+                                                        int32_t n_walks, int32_t which,
+                                                        uint8_t *term_ranks, int32_t *rank_sums)
+{
+    const int64_t walk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     if (walk >= n_walks) return;
     const tsf_walk_header *h = hdr + walk;
     const int m = h->m, n = h->n, p = h->p;
@@ -292,30 +393,49 @@ __global__ void __launch_bounds__(64) invariants_kernel(const tsf_walk_header *h
         return;
     }
     const bool z2 = h->mode == 1;
-    int32_t *M = scratch + lane * 64;
-    int s0 = 0, s1 = 0, s2 = 0;
     const uint64_t *sc = schemes + (size_t)walk * cap * 6;
     uint8_t *out = term_ranks + (size_t)walk * cap * 3;
-    for (int k = lane; k < rank; k += 64) {
-        const int a = factor_rank(sc[k * 6 + 0], sc[k * 6 + 1], m, n, z2, M);
-        const int b = factor_rank(sc[k * 6 + 2], sc[k * 6 + 3], n, p, z2, M);
-        const int c = factor_rank(sc[k * 6 + 4], sc[k * 6 + 5], p, m, z2, M);
-        out[k * 3 + 0] = (uint8_t)a;
-        out[k * 3 + 1] = (uint8_t)b;
-        out[k * 3 + 2] = (uint8_t)c;
-        s0 += a;
-        s1 += b;
-        s2 += c;
+    // per kind: rows, columns, row starts, reciprocal of the columns
+    const int rows[3] = {m, n, p}, cols[3] = {n, p, m};
+    uint64_t starts[3];
+    uint32_t magic[3];
+#pragma unroll
+    for (int X = 0; X < 3; ++X) {
+        starts[X] = 0;
+        for (int r = 0; r < rows[X]; ++r) starts[X] |= 1ull << (r * cols[X]);
+        magic[X] = (65536u + cols[X] - 1) / cols[X];
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        s0 += __shfl_xor(s0, off);
-        s1 += __shfl_xor(s1, off);
-        s2 += __shfl_xor(s2, off);
+    const bool al = (reinterpret_cast<uintptr_t>(sc) & 15) == 0;
+    int sum[3] = {0, 0, 0};
+    int X = lane % 3;
+    for (int q = lane; q < 3 * rank; q += 64) {
+        uint64_t d, s;
+        if (al) {
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(sc + 2 * q);
+            d = v.x;
+            s = v.y;
+        } else {
+            d = sc[2 * q];
+            s = sc[2 * q + 1];
+        }
+        const int R = X == 0 ? rows[0] : X == 1 ? rows[1] : rows[2];
+        const int Cc = X == 0 ? cols[0] : X == 1 ? cols[1] : cols[2];
+        const uint64_t lim = R * Cc == 64 ? ~0ull : (1ull << (R * Cc)) - 1;
+        d &= lim;
+        s &= d;
+        int a = factor_rank_masks(d, s, R, Cc, z2, X == 0 ? starts[0] : X == 1 ? starts[1] : starts[2],
+                                  X == 0 ? magic[0] : X == 1 ? magic[1] : magic[2]);
+        if (a < 0) a = factor_rank_entries(d, s, R, Cc);
+        out[q] = (uint8_t)a;
+        sum[0] += X == 0 ? a : 0;
+        sum[1] += X == 1 ? a : 0;
+        sum[2] += X == 2 ? a : 0;
+        X = X == 2 ? 0 : X + 1;  // 64 mod 3 = 1
     }
-    if (lane == 0) {
-        rank_sums[walk * 3 + 0] = s0;
-        rank_sums[walk * 3 + 1] = s1;
-        rank_sums[walk * 3 + 2] = s2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        for (int off = 32; off > 0; off >>= 1) sum[k] += __shfl_xor(sum[k], off);
+        if (lane == k) rank_sums[walk * 3 + k] = sum[k];
     }
 }
 
@@ -795,7 +915,7 @@ tsf_status tsf_walk_init(tsf_ctx *ctx, const tsf_walk_batch *b, void *hip_stream
     if (st) return st;
     if (b->n_walks == 0) return TSF_OK;
     hipStream_t s = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(init_kernel, dim3(b->n_walks), dim3(64), 0, s, b->hdr, b->cur, b->best,
+    hipLaunchKernelGGL(init_kernel, dim3((b->n_walks + 3) / 4), dim3(256), 0, s, b->hdr, b->cur, b->best,
                        b->start, b->n_walks, b->capacity);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "init launch failed");
     return TSF_OK;
@@ -1276,7 +1396,7 @@ tsf_status tsf_invariants_batch(const tsf_walk_batch *b, int32_t which, uint8_t 
     if (b->n_walks == 0) return TSF_OK;
     if (!term_ranks || !rank_sums) return tsf_fail(TSF_E_ARG, "null output");
     const uint64_t *src = which == 0 ? b->cur : which == 1 ? b->best : b->start;
-    hipLaunchKernelGGL(invariants_kernel, dim3(b->n_walks), dim3(64), 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL(invariants_kernel, dim3((b->n_walks + 3) / 4), dim3(256), 0, (hipStream_t)hip_stream,
                        b->hdr, src, b->capacity, b->n_walks, which, term_ranks, rank_sums);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "invariants launch failed");
     return TSF_OK;
@@ -1291,8 +1411,11 @@ tsf_status tsf_verify_batch(const tsf_walk_batch *b, int32_t which, int64_t *n_v
     if (!n_violated && b->n_walks) return tsf_fail(TSF_E_ARG, "null output");
     if (b->n_walks == 0) return TSF_OK;
     const uint64_t *src = which == 0 ? b->cur : which == 1 ? b->best : b->start;
-    hipLaunchKernelGGL(verify_kernel, dim3(b->n_walks), dim3(256), 0, (hipStream_t)hip_stream,
-                       b->hdr, src, b->capacity, b->n_walks, which, n_violated);
+    // four wavefronts (schemes) per workgroup, two where their LDS is large
+    const int all = (b->capacity + 63) / 64, waves = all <= 4 ? 4 : 2;
+    hipLaunchKernelGGL(verify_kernel, dim3((b->n_walks + waves - 1) / waves), dim3(64 * waves),
+                       waves * all * kVerifyLds, (hipStream_t)hip_stream, b->hdr, src, b->capacity,
+                       b->n_walks, which, n_violated);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "verify launch failed");
     return TSF_OK;
 }
