@@ -616,7 +616,8 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
                        uint16_t *d1, float *d3, float *loss, void *hip_stream);
 
 /* Walks with the learned proposal.  Each iteration: the first K = flip_tries
- * random attempts (K <= lanes_per_walk - 1, attempt-parallel strategy 1) each
+ * random attempts (K <= lanes_per_walk - 1, or 7 where the launch leaves the
+ * lanes to the library; attempt-parallel strategy 1) each
  * yield their candidate flip exactly as with uniform proposals; the network
  * scores the K candidates (rows of the same feature layout as
  * tsf_features_from_log) and the walk applies the highest-scored one (ties:
@@ -624,11 +625,12 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
  * search runs.  Everything else in the iteration is unchanged, so every scheme
  * is exact and verified as before.  The attempts counter grows by K per
  * iteration.  Workspace (device, caller-owned), R = 8 * n_walks rows:
- * cand R uint32, feat R x 512 bf16, h1 and h2 R x 256 bf16, logit R fp32.
+ * cand R uint32, feat R x 512 bf16, h1 and h2 R x 256 bf16 (required, contents
+ * undefined), logit R fp32.
  * choice (optional, device): choice_cap bytes per walk; the attempt applied at
  * iteration t (255 = fallback) goes to w*choice_cap + t-1 while t <= choice_cap.
- * Runs n_iters iterations (each a propose kernel, the network, an apply
- * kernel), asynchronous on `hip_stream`.  Errors: TSF_E_ARG, TSF_E_CAPACITY,
+ * Runs n_iters iterations (each the network and a kernel that applies the
+ * choice and proposes the next candidates), asynchronous on `hip_stream`.  Errors: TSF_E_ARG, TSF_E_CAPACITY,
  * TSF_E_DEVICE. */
 typedef struct {
     uint32_t *cand;

@@ -681,6 +681,26 @@ tsf_status check_net(const tsf_mlp *net)
 
 }  // namespace
 
+tsf_status mlp_forward(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_t *h1,
+                       uint16_t *h2, float *logit, void *hip_stream)
+{
+    tsf_status st = check_net(net);
+    if (st) return st;
+    if (M == 0) return TSF_OK;
+    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
+    const FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
+                    net->param + O_B2, net->param + O_B3, M, h1, h2, logit};
+    const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2);
+    const int rows = al ? rows_per_block(M) : 32;
+    auto *fn = !al ? fwd_kernel<1, 1, false> : rows == 128 ? fwd_kernel<2, 2, true>
+                                             : rows == 64 ? fwd_kernel<1, 2, true>
+                                                          : fwd_kernel<1, 1, true>;
+    hipLaunchKernelGGL(fn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0,
+                       (hipStream_t)hip_stream, g);
+    if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "forward launch failed");
+    return TSF_OK;
+}
+
 extern "C" {
 
 tsf_status tsf_mlp_sync(const tsf_mlp *net, void *hip_stream)
@@ -699,19 +719,7 @@ tsf_status tsf_mlp_fwd(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_
     tsf_status st = check_net(net);
     if (st) return st;
     if (M < 0 || (M > 0 && (!X || !h1 || !h2 || !logit))) return tsf_fail(TSF_E_ARG, "bad forward arguments");
-    if (M == 0) return TSF_OK;
-    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
-    const FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
-                    net->param + O_B2, net->param + O_B3, M, h1, h2, logit};
-    const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2);
-    const int rows = al ? rows_per_block(M) : 32;
-    auto *fn = !al ? fwd_kernel<1, 1, false> : rows == 128 ? fwd_kernel<2, 2, true>
-                                             : rows == 64 ? fwd_kernel<1, 2, true>
-                                                          : fwd_kernel<1, 1, true>;
-    hipLaunchKernelGGL(fn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0,
-                       (hipStream_t)hip_stream, g);
-    if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "forward launch failed");
-    return TSF_OK;
+    return mlp_forward(net, X, M, h1, h2, logit, hip_stream);
 }
 
 tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, int32_t M,

@@ -1218,15 +1218,34 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
         return tsf_fail(TSF_E_ARG, "learned proposals use the attempt-parallel strategy 1");
     if (prm && prm->objective != TSF_OBJ_RANK)
         return tsf_fail(TSF_E_ARG, "learned proposals serve the rank objective only");
-    tsf_status st = prepare_walk(prm, b, n_iters, &la, a, L);
-    if (st) return st;
+    // Lanes per walk where the call leaves them open: an iteration is bound by
+    // the latency of one wavefront, which grows with the walks in it (4,096
+    // (3,3,3) walks: 32.1 us an iteration with 32 lanes, 33.2 with 16, 38.3 with
+    // 8; 16,384 walks 91, 84 and 87).  The attempts scored stay those of 8.
+    const int lanes = la.lanes_per_walk;
+    if (lanes == 0 && b) la.lanes_per_walk = b->n_walks <= 4096 ? 32 : 16;
+    tsf_status st;
+    for (;;) {
+        st = prepare_walk(prm, b, n_iters, &la, a, L);
+        if (st) return st;
+        // the staged feature rows, beside the terms; fewer wavefronts share a
+        // workgroup where both do not fit (one always does)
+        L.lds += (size_t)(L.block.x / L.g) * 12 * kLearnRows * sizeof(uint64_t);
+        if (L.lds <= 160 * 1024 || L.block.x == 64) break;
+        la.waves_per_block = (int)L.block.x / 64 - 1;
+    }
+    if (L.lds > 64 * 1024 &&
+        hipFuncSetAttribute((const void *)L.fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)L.lds) != hipSuccess)
+        return tsf_fail(TSF_E_DEVICE, "cannot raise the LDS limit to %zu bytes", L.lds);
     if (!L.ap)
         return tsf_fail(TSF_E_CAPACITY,
                         "learned proposals use the attempt-parallel strategy (capacity <= 64)");
     const int K = prm->flip_tries;
-    if (K > L.g - 1 || K > kLearnRows)
+    const int g = lanes ? L.g : 8;
+    if (K > g - 1 || K > kLearnRows)
         return tsf_fail(TSF_E_ARG, "flip_tries %d exceeds the %d attempts scored at %d lanes/walk",
-                        K, L.g - 1 < kLearnRows ? L.g - 1 : kLearnRows, L.g);
+                        K, g - 1 < kLearnRows ? g - 1 : kLearnRows, g);
     if (!net || !ws || !ws->cand || !ws->feat || !ws->h1 || !ws->h2 || !ws->logit)
         return tsf_fail(TSF_E_ARG, "null learned-proposal buffer");
     if (ws->choice && ws->choice_cap < 0) return tsf_fail(TSF_E_ARG, "choice_cap < 0");
@@ -1241,23 +1260,25 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
     a.choice_cap = ws->choice ? ws->choice_cap : 0;
     a.n_iters = 1;
     hipStream_t s = (hipStream_t)hip_stream;
-    // one learned iteration: propose, score, apply
-    auto iteration = [&](hipStream_t on) -> tsf_status {
-        tsf_status e;
-        a.phase = 1;
-        if ((e = run(L, a, on))) return e;
-        if ((e = tsf_mlp_fwd(net, ws->feat, (int32_t)rows, ws->h1, ws->h2, ws->logit, on)))
-            return e;
-        a.phase = 2;
+    const auto walks = [&](int phase, hipStream_t on) -> tsf_status {
+        a.phase = phase;
         return run(L, a, on);
     };
-    // Every iteration launches the same kernels with the same arguments (the
-    // walk state lives in device memory), so a chunk of iterations is
-    // captured once into a HIP graph and replayed.
+    // score the proposed candidates, then apply the best and, but in the call's
+    // last iteration, propose the next ones: the scheme is loaded once an
+    // iteration.  The hidden layers stay in the network's kernel.
+    auto iteration = [&](hipStream_t on, bool last) -> tsf_status {
+        const tsf_status e = mlp_forward(net, ws->feat, (int32_t)rows, nullptr, nullptr, ws->logit, on);
+        return e ? e : walks(last ? 2 : 3, on);
+    };
+    if ((st = walks(1, s))) return st;
+    // Every iteration but the last launches the same kernels with the same
+    // arguments (the walk state lives in device memory), so a chunk of
+    // iterations is captured once into a HIP graph and replayed.
     const int64_t chunk = 16;
-    if (!ctx || n_iters < chunk) {
+    if (!ctx || n_iters <= chunk) {
         for (int64_t it = 0; it < n_iters; ++it)
-            if ((st = iteration(s))) return st;
+            if ((st = iteration(s, it + 1 == n_iters))) return st;
         return TSF_OK;
     }
     unsigned char key[sizeof(GraphEntry::key)];
@@ -1281,7 +1302,7 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
         if (hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return tsf_fail(TSF_E_DEVICE, "stream capture failed to start");
         for (int64_t it = 0; it < chunk; ++it)
-            if ((st = iteration(ctx->capture))) {
+            if ((st = iteration(ctx->capture, false))) {
                 hipGraph_t dummy;
                 hipStreamEndCapture(ctx->capture, &dummy);
                 if (dummy) hipGraphDestroy(dummy);
@@ -1298,11 +1319,11 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
         ge->used = true;
     }
     int64_t done = 0;
-    for (; done + chunk <= n_iters; done += chunk)
+    for (; done + chunk < n_iters; done += chunk)
         if (hipGraphLaunch(ge->exec, s) != hipSuccess)
             return tsf_fail(TSF_E_DEVICE, "graph launch failed");
     for (; done < n_iters; ++done)
-        if ((st = iteration(s))) return st;
+        if ((st = iteration(s, done + 1 == n_iters))) return st;
     return TSF_OK;
 }
 

@@ -84,7 +84,8 @@ struct KArgs {
     const float *logit;  // 8 per walk
     uint8_t *choice;     // choice_cap per walk, optional
     int32_t choice_cap;
-    int32_t phase;       // 0: n_iters uniform iterations; 1: propose; 2: apply
+    int32_t phase;       // 0: n_iters uniform iterations; 1: propose; 2: apply;
+                         // 3: apply, then propose for the next iteration
 };
 
 constexpr int kLearnRows = 8;  // candidate rows per walk in the learned workspace
@@ -281,7 +282,7 @@ struct Walker {
     int gshift;  // first lane of the group within the wavefront
     int cap2;
     T *lds;
-    uint64_t *mk;  // IX: match masks, mk[X*capm + k]
+    uint64_t *mk;  // IX: match masks, mk[X*capm + k]; learned: staged feature rows
     int capm;      // IX: row stride of the masks (the capacity)
     // walk scalars, identical in every lane of the group
     uint64_t seed;
@@ -2045,6 +2046,7 @@ struct Walker {
         const bool gate_lane = gl == G - 1;
         pb = draw(gate_lane ? 0u : (uint32_t)gl, gate_lane ? 1u : 0u);
         const int K = a->learn_k;
+        uint64_t *rows = mk;  // the walk's staged rows: 12 words per candidate
         uint32_t desc = ~0u;
         if (r >= 2) {
             update_scan_end();
@@ -2065,18 +2067,25 @@ struct Walker {
                 const int A = X == 0 ? 1 : 0, B = X == 2 ? 1 : 2;
                 const int Y = role ? B : A, Z = role ? A : B;
                 const TV<T> fv[6] = {ld(i, X), ld(i, Y), ld(i, Z), ld(j, X), ld(j, Y), ld(j, Z)};
-                uint64_t f[12];
 #pragma unroll
                 for (int q = 0; q < 6; ++q) {
-                    f[2 * q] = (uint64_t)fv[q].d;
-                    f[2 * q + 1] = (uint64_t)fv[q].s;
+                    rows[12 * gl + 2 * q] = (uint64_t)fv[q].d;
+                    rows[12 * gl + 2 * q + 1] = (uint64_t)fv[q].s;
                 }
-                uint16_t *row = a->feat + ((size_t)walk * kLearnRows + gl) * 512;
-#pragma unroll 1
-                for (int e = 0; e < 64; ++e) {
-                    const int b = e < 48 ? e >> 3 : 0;
-                    store_feature_piece(row, e, feature_piece(e, f[2 * b], f[2 * b + 1], fmt_slot, r));
-                }
+            }
+        }
+        // the group writes its rows one after another, 16 bytes a lane: eight
+        // lanes fill a line of memory (a lane per row took a store of 16 bytes
+        // to 64 rows at a time)
+        wave_lds_sync();
+        for (uint64_t live = gballot(desc != ~0u); live; live &= live - 1) {
+            const int row = __builtin_ctzll(live);
+            uint16_t *out = a->feat + ((size_t)walk * kLearnRows + row) * 512;
+#pragma unroll
+            for (int e = gl; e < 64; e += G) {
+                const int blk = e < 48 ? e >> 3 : 0;
+                store_feature_piece(out, e, feature_piece(e, rows[12 * row + 2 * blk],
+                                                          rows[12 * row + 2 * blk + 1], fmt_slot, r));
             }
         }
         if (gl < kLearnRows) a->cand[(size_t)walk * kLearnRows + gl] = desc;
@@ -2178,7 +2187,7 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     const int slot = uni(wave * W + grp);
     wk.lds = smem + (size_t)slot * a.cap2 * 3 * Wk::kFW;
     wk.mk = reinterpret_cast<uint64_t *>(smem + (size_t)wpb * W * a.cap2 * 3 * Wk::kFW) +
-            (size_t)slot * a.capm * 3;
+            (size_t)slot * (IX ? a.capm * 3 : 12 * kLearnRows);
     wk.a = &a;
     wk.walk = walk;
     tsf_walk_header *h = a.hdr + walk;
@@ -2247,11 +2256,18 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
             return;
         }
     }
-    if (AP && !IX && a.phase == 2) {
-        if (wk.reached()) done = 1;
-        if (!done && wk.t < a.max_iters) {
-            wk.t += 1;
-            if constexpr (AP && !IX) wk.apply_learned();
+    if (AP && !IX && a.phase >= 2) {
+        if constexpr (AP && !IX) {
+            if (wk.reached()) done = 1;
+            if (!done && wk.t < a.max_iters) {
+                wk.t += 1;
+                wk.apply_learned();
+                if (a.phase == 3 && !wk.reached() && wk.t < a.max_iters) {
+                    wk.t += 1;
+                    wk.propose();
+                    wk.t -= 1;
+                }
+            }
         }
     } else {
         // the call's last iteration, within the walk's budget
