@@ -8,11 +8,20 @@
 // ascending; after a term every equation it touches must stay reachable,
 // |target - partial sum| <= the number of later terms touching it.  The
 // patterns of the first P terms, read as one mixed-radix number (term 0 most
-// significant), name a subtree; one wavefront searches one subtree depth
-// first with the residuals of all equations in LDS, the lanes sharing the
-// products of a term.  The first solution in the global order is the one in
-// the smallest subtree that has a solution, provided every smaller subtree
-// was searched to the end.
+// significant), name a subtree; one wavefront searches one subtree depth first
+// with the residuals of all equations in LDS.  At a term the lanes try 64
+// patterns at once: each lane walks the term's products, whose equations and
+// sign masks come from a table the host lays out (uniform, so scalar loads and
+// LDS broadcasts), and a ballot gives the set of patterns that keep every
+// equation reachable; the search then takes its members in order, and a term's
+// set stays valid until the search leaves that term upwards.  LDS is sized by
+// the scheme's equations, so that a CU holds as many wavefronts as it has
+// slots.  16,384 subtrees of (2,2,3) schemes, 256 nodes each: 95-170 us a call
+// for most schemes, of which about 60 are its fixed cost (650-1,280 us with a
+// pattern at a time, every trial written to LDS and taken back, and 36 KiB of
+// LDS a wavefront); with 16,384 nodes each 0.8-4 ms (37-199 ms).  The first solution in the global order is the one in the
+// smallest subtree that has a solution, provided every smaller subtree was
+// searched to the end.
 #include <hip/hip_runtime.h>
 
 #include "../../include/tsf.h"
@@ -28,176 +37,166 @@ namespace {
 constexpr int kLiftMaxEq = 8192;     // equations (mn)(np)(pm) searched on the GPU
 constexpr int kLiftMaxTerms = 512;
 
-struct LiftArgs {
-    const uint64_t *d;      // r x 3 supports (u, v, w)
-    int m, n, p, r, P;      // format, rank, prefix terms
-    int64_t n_sub;          // subtrees
-    int64_t max_nodes;      // per subtree
-    int32_t *status;        // per subtree: 0 none, 1 found, 2 budget, 3 skipped
-    unsigned long long *first;  // smallest subtree id with a solution
-    uint64_t *signs;        // r x 3 sign masks of the solution (replay pass)
-    int64_t replay;         // >= 0: search this subtree only and write its signs
+// What a search leaves: the smallest subtree with a solution, the smallest that
+// ran out of budget, the number searched to the end.
+struct LiftOut {
+    unsigned long long first, budget, exhausted;
 };
 
-__device__ __forceinline__ int nth_bit(uint64_t m, int k)
-{
-    for (int q = 0; q < k; ++q) m &= m - 1;
-    return __builtin_ctzll(m);
-}
+struct LiftArgs {
+    const uint64_t *mask;   // per product: the pattern bits whose parity is its sign
+    const uint16_t *eq;     // per product: its equation
+    const int32_t *off;     // per term: its first product (r + 1 entries)
+    const int32_t *nfree;   // per term: its free signs
+    const int16_t *rem0;    // per equation: the products that touch it
+    int m, n, p, r, P, E;   // format, rank, prefix terms, equations
+    int64_t n_sub;          // subtrees
+    int64_t max_nodes;      // per subtree
+    LiftOut *out;
+    int64_t *pat;           // pattern per term of the solution (replay pass)
+    int replay;             // search subtree out->first only and write its patterns
+};
 
 struct LiftWave {
     const LiftArgs *a;
     int lane;
-    int Lv, Lw;
-    int16_t *res, *rem;
-    int64_t *pat;           // pattern per term
-    uint8_t *nfree;         // free signs per term
-
-    __device__ uint64_t du(int l) const { return a->d[l * 3 + 0]; }
-    __device__ uint64_t dv(int l) const { return a->d[l * 3 + 1]; }
-    __device__ uint64_t dw(int l) const { return a->d[l * 3 + 2]; }
-
-    // sign masks of term l under pattern x
-    __device__ void sign_masks(int l, int64_t x, uint64_t &su, uint64_t &sv, uint64_t &sw) const
-    {
-        const uint64_t u = du(l), v = dv(l), w = dw(l);
-        const int cu = __builtin_popcountll(u), cv = __builtin_popcountll(v);
-        su = sv = sw = 0;
-        int bit = 0;
-        uint64_t q = u & (u - 1);   // u without its first entry
-        for (; q; q &= q - 1, ++bit)
-            if ((x >> bit) & 1) su |= q & (~q + 1);
-        q = v & (v - 1);
-        for (; q; q &= q - 1, ++bit)
-            if ((x >> bit) & 1) sv |= q & (~q + 1);
-        for (q = w; q; q &= q - 1, ++bit)
-            if ((x >> bit) & 1) sw |= q & (~q + 1);
-        (void)cu;
-        (void)cv;
-    }
+    int16_t *res, *rem;     // per equation: target - partial sum, later products
 
     // add (dir -1) or remove (+1) term l's products under pattern x; returns
     // whether every touched equation stays reachable (when adding)
     __device__ bool apply(int l, int64_t x, int dir)
     {
-        uint64_t su, sv, sw;
-        sign_masks(l, x, su, sv, sw);
-        const uint64_t u = du(l), v = dv(l), w = dw(l);
-        const int cu = __builtin_popcountll(u), cv = __builtin_popcountll(v),
-                  cw = __builtin_popcountll(w);
-        const int total = cu * cv * cw;
         bool ok = true;
-        for (int c = lane; c < total; c += 64) {
-            const int qa = c / (cv * cw), qb = (c / cw) % cv, qc = c % cw;
-            const int ea = nth_bit(u, qa), eb = nth_bit(v, qb), ec = nth_bit(w, qc);
-            const int neg = (int)(((su >> ea) ^ (sv >> eb) ^ (sw >> ec)) & 1);
-            const int e = (ea * Lv + eb) * Lw + ec;
+        for (int c = a->off[l] + lane; c < a->off[l + 1]; c += 64) {
+            const int e = a->eq[c];
+            const int neg = __builtin_popcountll((uint64_t)x & a->mask[c]) & 1;
             const int r2 = res[e] + dir * (neg ? -1 : 1);
             const int m2 = rem[e] + dir;
             res[e] = (int16_t)r2;
             rem[e] = (int16_t)m2;
             if (dir < 0 && (r2 > m2 || -r2 > m2)) ok = false;
         }
+        sync();
+        return __ballot(!ok) == 0;
+    }
+    // the patterns of term l in 64 consecutive ones from x0 on that keep every
+    // equation reachable
+    __device__ uint64_t feasible(int l, int64_t x0) const
+    {
+        const int64_t x = x0 + lane;
+        bool ok = x < (1ll << a->nfree[l]);
+        const int end = a->off[l + 1];
+        for (int c = a->off[l]; c < end; ++c) {
+            const int e = a->eq[c];
+            const int r1 = res[e], m2 = rem[e] - 1;
+            const int r2 = r1 - 1 + 2 * (__builtin_popcountll((uint64_t)x & a->mask[c]) & 1);
+            ok = ok && r2 <= m2 && -r2 <= m2;
+        }
+        return __ballot(ok);
+    }
+    __device__ __forceinline__ static void sync()
+    {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        return __ballot(!ok) == 0;
     }
 };
 
+// LDS of a search: two counters per equation, a pattern and a set per term
+size_t lift_lds(int E, int r) { return (size_t)r * 16 + (size_t)E * 4; }
+
 __global__ void __launch_bounds__(64) lift_kernel(LiftArgs a)
 {
-    __shared__ int16_t res[kLiftMaxEq], rem[kLiftMaxEq];
-    __shared__ int64_t pat[kLiftMaxTerms];
-    __shared__ uint8_t nfree[kLiftMaxTerms];
-    const int64_t sub = a.replay >= 0 ? a.replay : (int64_t)blockIdx.x;
+    extern __shared__ uint64_t lift_smem[];
+    uint64_t *set = lift_smem;                              // per term
+    int64_t *pat = reinterpret_cast<int64_t *>(set + a.r);  // per term
+    int16_t *res = reinterpret_cast<int16_t *>(pat + a.r), *rem = res + a.E;
     const int lane = threadIdx.x;
+    const unsigned long long known = a.replay ? a.out->first : 0;
+    if (a.replay && known == ~0ull) return;  // nothing was found
+    const int64_t sub = a.replay ? (int64_t)known : (int64_t)blockIdx.x;
     if (sub >= a.n_sub) return;
-    int32_t *st = a.status + (a.replay >= 0 ? 0 : sub);
-    LiftWave W{&a, lane, a.n * a.p, a.p * a.m, res, rem, pat, nfree};
-    const int Lu = a.m * a.n, E = Lu * W.Lv * W.Lw;
+    LiftWave W{&a, lane, res, rem};
+    const int Lv = a.n * a.p, Lw = a.p * a.m;
     // targets and contributor counts
-    for (int e = lane; e < E; e += 64) {
-        const int ea = e / (W.Lv * W.Lw), eb = (e / W.Lw) % W.Lv, ec = e % W.Lw;
+    for (int e = lane; e < a.E; e += 64) {
+        const int ea = e / (Lv * Lw), eb = (e / Lw) % Lv, ec = e % Lw;
         const int a1 = ea / a.n, a2 = ea % a.n, b1 = eb / a.p, b2 = eb % a.p, c1 = ec / a.m,
                   c2 = ec % a.m;
         res[e] = (a2 == b1 && b2 == c1 && c2 == a1) ? 1 : 0;
-        rem[e] = 0;
-    }
-    for (int l = lane; l < a.r; l += 64)
-        nfree[l] = (uint8_t)(__builtin_popcountll(W.du(l)) - 1 + __builtin_popcountll(W.dv(l)) - 1 +
-                             __builtin_popcountll(W.dw(l)));
-    __syncthreads();
-    for (int l = 0; l < a.r; ++l) {
-        const uint64_t u = W.du(l), v = W.dv(l), w = W.dw(l);
-        const int cv = __builtin_popcountll(v), cw = __builtin_popcountll(w);
-        const int total = __builtin_popcountll(u) * cv * cw;
-        for (int c = lane; c < total; c += 64) {
-            const int e = (nth_bit(u, c / (cv * cw)) * W.Lv + nth_bit(v, (c / cw) % cv)) * W.Lw +
-                          nth_bit(w, c % cw);
-            rem[e] = (int16_t)(rem[e] + 1);
-        }
-        __syncthreads();
+        rem[e] = a.rem0[e];
     }
     // the subtree's prefix: patterns of terms 0..P-1 from the mixed-radix id
     int64_t rest = sub;
     for (int l = a.P - 1; l >= 0; --l) {
-        const int64_t radix = 1ll << nfree[l];
-        if (lane == 0) pat[l] = rest % radix;
-        rest /= radix;
+        if (lane == 0) pat[l] = rest & ((1ll << a.nfree[l]) - 1);
+        rest >>= a.nfree[l];
     }
-    __syncthreads();
+    LiftWave::sync();
     bool alive = true;
     for (int l = 0; l < a.P && alive; ++l) alive = W.apply(l, pat[l], -1);
-    int status = alive ? 0 : 0;
-    int64_t nodes = 0;
+    int status = 0;  // 0 searched to the end, 1 found, 2 budget, 3 a smaller subtree has one
     if (alive) {
         int l = a.P;
-        int64_t x = 0;
+        int64_t nodes = 0, x = 0;  // x: the next pattern of term l
         bool found = a.P == a.r;
-        while (!found) {
-            // another wavefront found a solution in a smaller subtree
-            if (a.replay < 0 && (nodes & 255) == 0 &&
-                __atomic_load_n(a.first, __ATOMIC_RELAXED) < (unsigned long long)sub) {
+        for (uint32_t turn = 0; !found; ++turn) {
+            if (!a.replay && (turn & 63) == 0 &&
+                __atomic_load_n(&a.out->first, __ATOMIC_RELAXED) < (unsigned long long)sub) {
                 status = 3;
                 break;
             }
-            if (x == (1ll << nfree[l])) {
-                // this level is exhausted: back to the previous free level
+            const int64_t end = 1ll << a.nfree[l];
+            uint64_t s = 0;
+            if (x < end) {
+                const int64_t block = x & ~63ll;
+                if (x == block) {  // entered from above or from the block before
+                    s = W.feasible(l, block);
+                    if (lane == 0) set[l] = s;
+                    LiftWave::sync();
+                } else {
+                    s = set[l];
+                }
+                // members from x on; the patterns passed over are nodes too
+                s &= ~0ull << (x & 63);
+                const int64_t next = s ? block + __builtin_ctzll(s)
+                                       : (block + 64 < end ? block + 64 : end);
+                nodes += next - x;
+                if (s ? nodes >= a.max_nodes : nodes > a.max_nodes) {
+                    status = 2;
+                    break;
+                }
+                x = next;
+                if (s == 0 && x < end) continue;
+            }
+            if (s == 0) {
+                // this term is exhausted: back to the previous free one
                 if (l == a.P) break;
                 --l;
-                W.apply(l, pat[l], +1);
-                x = pat[l] + 1;
+                x = pat[l];
+                W.apply(l, x, +1);
+                ++x;
                 continue;
-            }
-            if (nodes >= a.max_nodes) {
-                status = 2;
-                break;
             }
             ++nodes;
             if (lane == 0) pat[l] = x;
-            __syncthreads();
-            if (W.apply(l, x, -1)) {
-                ++l;
-                x = 0;
-                found = l == a.r;
-            } else {
-                W.apply(l, x, +1);
-                ++x;
-            }
+            W.apply(l, x, -1);
+            ++l;
+            x = 0;
+            found = l == a.r;
         }
         if (found) status = 1;
     }
-    if (lane == 0) *st = status;
-    if (status == 1 && lane == 0 && a.replay < 0) atomicMin(a.first, (unsigned long long)sub);
-    if (status == 1 && a.replay >= 0)
-        for (int l = lane; l < a.r; l += 64) {
-            uint64_t su, sv, sw;
-            W.sign_masks(l, pat[l], su, sv, sw);
-            a.signs[l * 3 + 0] = su;
-            a.signs[l * 3 + 1] = sv;
-            a.signs[l * 3 + 2] = sw;
-        }
+    if (a.replay) {
+        if (status == 1)
+            for (int l = lane; l < a.r; l += 64) a.pat[l] = pat[l];
+        return;
+    }
+    if (lane == 0) {
+        if (status == 1) atomicMin(&a.out->first, (unsigned long long)sub);
+        if (status == 2) atomicMin(&a.out->budget, (unsigned long long)sub);
+        if (status <= 1) atomicAdd(&a.out->exhausted, 1ull);
+    }
 }
 
 }  // namespace
@@ -239,72 +238,108 @@ tsf_status tsf_lift(const tsf_scheme *z2, int64_t max_nodes, int32_t max_subtree
     int P = 0;
     int64_t n_sub = 1;
     while (P < r && n_sub * (1ll << nfree[P]) <= max_subtrees) n_sub *= 1ll << nfree[P++];
-    uint64_t *d_d = nullptr, *d_signs = nullptr;
-    int32_t *d_status = nullptr;
-    unsigned long long *d_first = nullptr;
-    tsf_status st = TSF_OK;
-    if (hipMalloc(&d_d, d.size() * 8) != hipSuccess || hipMalloc(&d_signs, d.size() * 8) != hipSuccess ||
-        hipMalloc(&d_status, (size_t)n_sub * 4) != hipSuccess ||
-        hipMalloc(&d_first, 8) != hipSuccess) {
-        st = tsf_fail(TSF_E_DEVICE, "lift buffers");
-    } else {
-        const unsigned long long none = ~0ull;
-        hipMemcpy(d_d, d.data(), d.size() * 8, hipMemcpyHostToDevice);
-        hipMemcpy(d_first, &none, 8, hipMemcpyHostToDevice);
-        LiftArgs a{d_d, m, n, p, r, P, n_sub, max_nodes, d_status, d_first, d_signs, -1};
-        hipLaunchKernelGGL(lift_kernel, dim3((unsigned)n_sub), dim3(64), 0, 0, a);
-        std::vector<int32_t> status((size_t)n_sub);
-        unsigned long long first = none;
-        if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-            hipMemcpy(status.data(), d_status, (size_t)n_sub * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(&first, d_first, 8, hipMemcpyDeviceToHost) != hipSuccess) {
-            st = tsf_fail(TSF_E_DEVICE, "lift search failed");
-        } else {
-            int64_t budget_first = -1;
-            for (int64_t q = 0; q < n_sub; ++q)
-                if (status[q] == 2) {
-                    budget_first = q;
-                    break;
+    // the products of every term, the contributor counts and the search's
+    // results, in one buffer: one allocation, one copy each way
+    const int Lv = len[1], Lw = len[2], E = len[0] * Lv * Lw;
+    std::vector<uint64_t> mask;
+    std::vector<uint16_t> eq;
+    std::vector<int32_t> off(1, 0);
+    std::vector<int16_t> rem(E, 0);
+    for (int l = 0; l < r; ++l) {
+        const uint64_t u = d[l * 3], v = d[l * 3 + 1], w = d[l * 3 + 2];
+        const int cu = __builtin_popcountll(u), cv = __builtin_popcountll(v);
+        int qa = 0;
+        for (uint64_t fu = u; fu; fu &= fu - 1, ++qa) {
+            int qb = 0;
+            for (uint64_t fv = v; fv; fv &= fv - 1, ++qb) {
+                int qc = 0;
+                for (uint64_t fw = w; fw; fw &= fw - 1, ++qc) {
+                    const int e = (__builtin_ctzll(fu) * Lv + __builtin_ctzll(fv)) * Lw +
+                                  __builtin_ctzll(fw);
+                    eq.push_back((uint16_t)e);
+                    mask.push_back((qa ? 1ull << (qa - 1) : 0) |
+                                   (qb ? 1ull << (cu - 1 + qb - 1) : 0) |
+                                   1ull << (cu - 1 + cv - 1 + qc));
+                    ++rem[e];
                 }
-            std::memset(res, 0, sizeof *res);
-            res->subtrees = n_sub;
-            res->prefix_terms = P;
-            for (int64_t q = 0; q < n_sub; ++q) res->exhausted += status[q] == 0 || status[q] == 1;
-            if (first != none) {
-                res->status = (budget_first < 0 || (int64_t)first < budget_first) ? 1 : 2;
-                res->subtree = (int64_t)first;
-                a.replay = (int64_t)first;
-                a.max_nodes = INT64_MAX;
-                hipLaunchKernelGGL(lift_kernel, dim3(1), dim3(64), 0, 0, a);
-                std::vector<uint64_t> s(d.size());
-                if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess ||
-                    hipMemcpy(s.data(), d_signs, s.size() * 8, hipMemcpyDeviceToHost) != hipSuccess) {
-                    st = tsf_fail(TSF_E_DEVICE, "lift replay failed");
-                } else {
-                    const int32_t out_cap = out->d.capacity;   // the caller's buffers
-                    out->d = z2->d;
-                    out->d.capacity = out_cap;
-                    out->d.mode = TSF_TERNARY;
-                    int8_t *om[3] = {out->U, out->V, out->W};
-                    for (int X = 0; X < 3; ++X)
-                        std::memset(om[X], 0, (size_t)out->d.capacity * len[X]);
-                    for (int l = 0; l < r; ++l)
-                        for (int X = 0; X < 3; ++X)
-                            for (int e = 0; e < len[X]; ++e)
-                                if ((d[l * 3 + X] >> e) & 1)
-                                    om[X][(size_t)l * len[X] + e] =
-                                        ((s[l * 3 + X] >> e) & 1) ? -1 : 1;
-                }
-            } else {
-                res->status = budget_first < 0 ? 0 : -1;
-                res->subtree = -1;
             }
         }
+        off.push_back((int32_t)eq.size());
     }
-    if (d_d) hipFree(d_d);
-    if (d_signs) hipFree(d_signs);
-    if (d_status) hipFree(d_status);
-    if (d_first) hipFree(d_first);
+    const size_t np = eq.size();
+    const size_t o_pat = sizeof(LiftOut), o_mask = o_pat + (size_t)r * 8, o_off = o_mask + np * 8,
+                 o_free = o_off + (size_t)(r + 1) * 4, o_eq = o_free + (size_t)r * 4,
+                 o_rem = o_eq + np * 2, bytes = o_rem + (size_t)E * 2;
+    std::vector<unsigned char> blob(bytes);
+    const LiftOut none{~0ull, ~0ull, 0};
+    std::memcpy(blob.data(), &none, sizeof none);
+    std::memset(blob.data() + o_pat, 0, (size_t)r * 8);
+    std::memcpy(blob.data() + o_mask, mask.data(), np * 8);
+    std::memcpy(blob.data() + o_off, off.data(), off.size() * 4);
+    std::memcpy(blob.data() + o_free, nfree.data(), nfree.size() * 4);
+    std::memcpy(blob.data() + o_eq, eq.data(), np * 2);
+    std::memcpy(blob.data() + o_rem, rem.data(), rem.size() * 2);
+    unsigned char *dev = nullptr;
+    if (hipMalloc(&dev, bytes) != hipSuccess) return tsf_fail(TSF_E_DEVICE, "lift buffers");
+    tsf_status st = TSF_OK;
+    LiftArgs a{(const uint64_t *)(dev + o_mask), (const uint16_t *)(dev + o_eq),
+               (const int32_t *)(dev + o_off), (const int32_t *)(dev + o_free),
+               (const int16_t *)(dev + o_rem), m, n, p, r, P, E, n_sub, max_nodes,
+               (LiftOut *)dev, (int64_t *)(dev + o_pat), 0};
+    const size_t lds = lift_lds(E, r);
+    const bool sent = hipMemcpy(dev, blob.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+    if (sent) {
+        // the search, then the patterns of the smallest subtree that has a
+        // solution (no budget: the search found it)
+        hipLaunchKernelGGL(lift_kernel, dim3((unsigned)n_sub), dim3(64), lds, 0, a);
+        a.replay = 1;
+        a.max_nodes = INT64_MAX;
+        hipLaunchKernelGGL(lift_kernel, dim3(1), dim3(64), lds, 0, a);
+    }
+    std::vector<unsigned char> back(o_mask);
+    if (!sent || hipGetLastError() != hipSuccess ||
+        hipMemcpy(back.data(), dev, o_mask, hipMemcpyDeviceToHost) != hipSuccess) {
+        st = tsf_fail(TSF_E_DEVICE, "lift search failed");
+    } else {
+        LiftOut got;
+        std::memcpy(&got, back.data(), sizeof got);
+        std::memset(res, 0, sizeof *res);
+        res->subtrees = n_sub;
+        res->prefix_terms = P;
+        res->exhausted = (int64_t)got.exhausted;
+        if (got.first != ~0ull) {
+            res->status = got.first < got.budget ? 1 : 2;
+            res->subtree = (int64_t)got.first;
+            const int32_t out_cap = out->d.capacity;   // the caller's buffers
+            out->d = z2->d;
+            out->d.capacity = out_cap;
+            out->d.mode = TSF_TERNARY;
+            int8_t *om[3] = {out->U, out->V, out->W};
+            for (int X = 0; X < 3; ++X) std::memset(om[X], 0, (size_t)out->d.capacity * len[X]);
+            for (int l = 0; l < r; ++l) {
+                int64_t x;
+                std::memcpy(&x, back.data() + o_pat + (size_t)l * 8, 8);
+                // the first entries of u and v are +1, the others as the
+                // pattern's bits say
+                for (int X = 0; X < 3; ++X) {
+                    bool first = X < 2;
+                    for (uint64_t f = d[l * 3 + X]; f; f &= f - 1) {
+                        int sign = 1;
+                        if (!first) {
+                            sign = x & 1 ? -1 : 1;
+                            x >>= 1;
+                        }
+                        first = false;
+                        om[X][(size_t)l * len[X] + __builtin_ctzll(f)] = (int8_t)sign;
+                    }
+                }
+            }
+        } else {
+            res->status = got.budget == ~0ull ? 0 : -1;
+            res->subtree = -1;
+        }
+    }
+    hipFree(dev);
     return st;
 }
 
