@@ -1,6 +1,7 @@
 """The lifting search's node budget against the oracle's count of nodes, in
 one tree (no prefix): with as many nodes as the oracle needed the GPU ends as
 it does, with one fewer it runs out."""
+import numpy as np
 import pytest
 
 from oracle import pyoracle as O
