@@ -241,10 +241,11 @@ __global__ void __launch_bounds__(256) verify_kernel(const tsf_walk_header *hdr,
 __device__ __forceinline__ uint64_t remap_mask(uint64_t mask, int cols, int cols2, int drop_r,
                                                int drop_c)
 {
+    const uint32_t by = div_by(cols);
     uint64_t o = 0;
     for (; mask; mask &= mask - 1) {
         const int e = __builtin_ctzll(mask);
-        const int rr = e / cols, cc = e % cols;
+        const int rr = div_entry(e, by), cc = e - rr * cols;
         if (rr == drop_r || cc == drop_c) continue;
         const int r2 = rr - (drop_r >= 0 && rr > drop_r), c2 = cc - (drop_c >= 0 && cc > drop_c);
         o |= 1ull << (r2 * cols2 + c2);
