@@ -991,7 +991,8 @@ tsf_launch default_launch(const tsf_walk_params *prm, const tsf_walk_batch *b)
 
 // validate a walk call and build its kernel arguments and launch shape
 tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int64_t n_iters,
-                        const tsf_launch *launch, KArgs &a, Launch &L, bool checked = false)
+                        const tsf_launch *launch, KArgs &a, Launch &L, bool checked = false,
+                        bool learned = false)
 {
     tsf_status st = check_batch(b);
     if (st) return st;
@@ -1043,7 +1044,7 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
     if (checked && g != (ap ? 8 : 64))
         return tsf_fail(TSF_E_ARG, "checked walks use %d lanes per walk with this strategy",
                         ap ? 8 : 64);
-    L.fn = pick_kernel(g, s, wide, b->mode == TSF_Z2, pk ? 4 : strategy, checked);
+    L.fn = pick_kernel(g, s, wide, b->mode == TSF_Z2, learned ? 5 : pk ? 4 : strategy, checked);
     if (!L.fn) return tsf_fail(TSF_E_ARG, "no kernel for this configuration");
     const size_t word = wide ? 8 : 4;
     const size_t factor_bytes = pk ? 4 : 2 * word;
@@ -1249,7 +1250,7 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
     if (lanes == 0 && b) la.lanes_per_walk = b->n_walks <= 4096 ? 32 : 16;
     tsf_status st;
     for (;;) {
-        st = prepare_walk(prm, b, n_iters, &la, a, L);
+        st = prepare_walk(prm, b, n_iters, &la, a, L, false, true);
         if (st) return st;
         // the staged feature rows, beside the terms; fewer wavefronts share a
         // workgroup where both do not fit (one always does)

@@ -72,12 +72,33 @@ KernelFn pick_ap(bool ix, int s, bool pk, bool chk)
     }
 }
 
+// the phases of learned proposals (plain attempt-parallel walks)
+template <int G>
+KernelFn pick_learned(int s)
+{
+    switch (s) {
+    case 1: return walk_learned_kernel<G, 1, Word, kZ2>;
+    case 2: return walk_learned_kernel<G, 2, Word, kZ2>;
+    default: return nullptr;
+    }
+}
+
 #define TSF_CAT2(a, b, c) pick_kernel_w##a##_z##b##c
 #define TSF_CAT(a, b) TSF_CAT2(a, b, )
 // strategy: 1 attempt-parallel, 2 term-parallel, 3 indexed attempt-parallel,
-// 4 indexed attempt-parallel with packed factors; chk: the checked variant
+// 4 indexed attempt-parallel with packed factors, 5 learned proposals; chk: the
+// checked variant
 KernelFn TSF_CAT(TSFK_WIDE, TSFK_Z2)(int g, int s, int strategy, bool chk)
 {
+    if (strategy == 5) {
+        switch (g) {
+        case 4: return pick_learned<4>(s);
+        case 8: return pick_learned<8>(s);
+        case 16: return pick_learned<16>(s);
+        case 32: return pick_learned<32>(s);
+        default: return nullptr;
+        }
+    }
     if (strategy == 1 || strategy == 3 || strategy == 4) {
         const bool ix = strategy >= 3, pk = strategy == 4;
         switch (g) {

@@ -2155,7 +2155,10 @@ __device__ __forceinline__ void progress_priority(int64_t it, int64_t n)
     else __builtin_amdgcn_s_setprio(0);
 }
 
-template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK, bool CHK>
+// LRN: the phases of a learned proposal in place of the iterations (a kernel of
+// its own: with both in one, the iterations' kernel needs 132 VGPRs, one more
+// than four wavefronts per SIMD have)
+template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK, bool CHK, bool LRN = false>
 __device__ __forceinline__ void walk_body(const KArgs &a)
 {
     extern __shared__ uint64_t smem_u64[];
@@ -2187,7 +2190,7 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     const int slot = uni(wave * W + grp);
     wk.lds = smem + (size_t)slot * a.cap2 * 3 * Wk::kFW;
     wk.mk = reinterpret_cast<uint64_t *>(smem + (size_t)wpb * W * a.cap2 * 3 * Wk::kFW) +
-            (size_t)slot * (IX ? a.capm * 3 : 12 * kLearnRows);
+            (size_t)slot * (LRN ? 12 * kLearnRows : a.capm * 3);
     wk.a = &a;
     wk.walk = walk;
     tsf_walk_header *h = a.hdr + walk;
@@ -2247,26 +2250,22 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
         }
     }
 
-    if constexpr (AP && !IX) {
+    if constexpr (LRN) {
         if (a.phase == 1) {
-            // learned proposal, phase 1: candidates and feature rows only
+            // candidates and feature rows only
             if (wk.reached() || wk.t >= a.max_iters) return;
             wk.t += 1;
             wk.propose();
             return;
         }
-    }
-    if (AP && !IX && a.phase >= 2) {
-        if constexpr (AP && !IX) {
-            if (wk.reached()) done = 1;
-            if (!done && wk.t < a.max_iters) {
+        if (wk.reached()) done = 1;
+        if (!done && wk.t < a.max_iters) {
+            wk.t += 1;
+            wk.apply_learned();
+            if (a.phase == 3 && !wk.reached() && wk.t < a.max_iters) {
                 wk.t += 1;
-                wk.apply_learned();
-                if (a.phase == 3 && !wk.reached() && wk.t < a.max_iters) {
-                    wk.t += 1;
-                    wk.propose();
-                    wk.t -= 1;
-                }
+                wk.propose();
+                wk.t -= 1;
             }
         }
     } else {
@@ -2314,14 +2313,25 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
 // are held to 128 VGPRs, four wavefronts per SIMD, which their LDS also
 // allows at (3,3,3) (10,176 bytes per 8-walk wavefront, sixteen per CU); the
 // other indexed kernels with 32-bit masks to 168 VGPRs (three per SIMD, as
-// many as their LDS allows); the rest are not constrained (the term-parallel
-// kernels with 64 lanes need 74 to 130).
+// many as their LDS allows), the plain attempt-parallel ones with 32-bit masks
+// to 128 (four per SIMD, as 88 terms at 16 lanes leave room for); the rest are
+// not constrained (the term-parallel kernels with 64 lanes need 74 to 130).
 template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK = false>
 __global__ void __launch_bounds__(256) __attribute__((
-    amdgpu_waves_per_eu(PK && G >= 8 ? 4 : (IX && G >= 8 && sizeof(T) == 4) ? 3 : 1)))
+    amdgpu_waves_per_eu((PK || (AP && !IX && sizeof(T) == 4)) && G >= 8 ? 4
+                        : (IX && G >= 8 && sizeof(T) == 4)               ? 3
+                                                                         : 1)))
 walk_kernel(KArgs a)
 {
     walk_body<G, S, T, Z2, AP, IX, PK, false>(a);
+}
+
+// one phase of a learned proposal on every walk (tsf_walk_learned)
+template <int G, int S, typename T, bool Z2>
+__global__ void __launch_bounds__(256) __attribute__((
+    amdgpu_waves_per_eu(G >= 8 && sizeof(T) == 4 ? 4 : 1))) walk_learned_kernel(KArgs a)
+{
+    walk_body<G, S, T, Z2, true, false, false, false, true>(a);
 }
 
 // the same walk with the invariant checks (tsf_walk_checked)
