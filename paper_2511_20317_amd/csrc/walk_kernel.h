@@ -272,7 +272,13 @@ struct Walker {
     // a fingerprint in a register (see the section FP below)
     static constexpr bool kFP = !AP && G == 64;
     uint32_t fp[kFP ? S : 1][3];
+    static constexpr bool kClose = kFP;
     bool fp_stale;  // the fingerprints do not describe the terms in LDS
+    // kClose: the lane's slots whose terms may agree with another term in two
+    // fingerprints (both terms of such a pair are in it), and whether this
+    // iteration's flip wrote a fingerprint that another term has
+    uint32_t close;
+    bool near;
     // kFP: pb holds the blocks of several iterations, 2^dsh lanes each (attempts
     // from the first lane on, the gates in the last); dbase: the first lane of
     // the current iteration, 64 before the next draw
@@ -285,17 +291,85 @@ struct Walker {
     uint64_t *mk;  // IX: match masks, mk[X*capm + k]; learned: staged feature rows
     int capm;      // IX: row stride of the masks (the capacity)
     // walk scalars, identical in every lane of the group
-    uint64_t seed;
-    int r, r_cap, best_rank, start_rank, target, n_rec;
+    int r, r_cap, best_rank;
     // additions objective: flips must keep every factor non-zero, the best
     // scheme is the one with the fewest non-zero coefficients
     bool additions;
-    int nnz, best_nnz, mp;
-    int64_t t, plateau_start;
+    int nnz;
+    int64_t t;
     int64_t restart_at;  // plateau_start + plateau, or never
     int64_t log_until;   // last iteration of the training log, 0 without one
     bool hit;            // the stop rule holds
-    uint32_t cnt[C_NUM];
+    // Scalars that are seldom used, and the counters of the call.  One walk per
+    // wavefront: word k is lane k of one vector register.  As scalars they and
+    // comparisons hoisted out of the loop left too few scalar registers for the
+    // iteration, and 65 (128 terms) to 90 (448) were spilled or read again from
+    // the arguments in every iteration; 5 to 18 are left.  65,536 (4,4,5) walks
+    // 37.7 -> 35.1 us an iteration, 8,192 (6,7,9) walks 15.1 -> 14.2.
+    enum {
+        K_TARGET,
+        K_MP,
+        K_START_RANK,
+        K_N_REC,
+        K_FMT_SLOT,
+        K_BEST_NNZ,
+        K_PLATEAU,  // two words
+        K_WALK = K_PLATEAU + 2,
+        K_SEED = K_WALK + 2,
+        K_CNT = K_SEED + 2,
+        K_NUM = K_CNT + C_NUM
+    };
+    uint32_t kept[kFP ? 1 : K_NUM];
+    // the lane, for comparisons that the compiler is to make where they are
+    // needed: kept from before the loop, every one occupies two scalar registers
+    __device__ __forceinline__ int here() const
+    {
+        int l = gl;
+        if constexpr (kFP) asm volatile("" : "+v"(l));
+        return l;
+    }
+    __device__ __forceinline__ uint32_t get(int k) const
+    {
+        if constexpr (kFP)
+            return (uint32_t)__builtin_amdgcn_readlane((int)kept[0], k);
+        else
+            return kept[k];
+    }
+    __device__ __forceinline__ void put(int k, uint32_t v)
+    {
+        if constexpr (kFP)
+            kept[0] = here() == k ? v : kept[0];
+        else
+            kept[k] = v;
+    }
+    __device__ __forceinline__ uint64_t get64(int k) const
+    {
+        return (uint64_t)get(k) | (uint64_t)get(k + 1) << 32;
+    }
+    __device__ __forceinline__ void put64(int k, uint64_t v)
+    {
+        put(k, (uint32_t)v);
+        put(k + 1, (uint32_t)(v >> 32));
+    }
+    __device__ __forceinline__ int target() const { return (int)get(K_TARGET); }
+    __device__ __forceinline__ int mp() const { return (int)get(K_MP); }
+    __device__ __forceinline__ int start_rank() const { return (int)get(K_START_RANK); }
+    __device__ __forceinline__ int n_rec() const { return (int)get(K_N_REC); }
+    __device__ __forceinline__ void set_n_rec(int v) { put(K_N_REC, (uint32_t)v); }
+    __device__ __forceinline__ int fmt_slot() const { return (int)get(K_FMT_SLOT); }
+    __device__ __forceinline__ int best_nnz() const { return (int)get(K_BEST_NNZ); }
+    __device__ __forceinline__ void set_best_nnz(int v) { put(K_BEST_NNZ, (uint32_t)v); }
+    __device__ __forceinline__ int64_t plateau_start() const { return (int64_t)get64(K_PLATEAU); }
+    __device__ __forceinline__ void set_plateau_start(int64_t v) { put64(K_PLATEAU, (uint64_t)v); }
+    __device__ __forceinline__ int64_t walk() const { return (int64_t)get64(K_WALK); }
+    __device__ __forceinline__ uint64_t seed() const { return get64(K_SEED); }
+    __device__ __forceinline__ void count(int c, uint32_t n)
+    {
+        if constexpr (kFP)
+            kept[0] += here() == K_CNT + c ? n : 0u;
+        else
+            kept[K_CNT + c] += n;
+    }
     const KArgs *a;
     // the arguments (the kernel's only one, so at the start of its argument
     // segment) for code that seldom runs: read from memory there, where the
@@ -308,17 +382,17 @@ struct Walker {
         asm volatile("" : "+s"(p));
         return *(const KArgs *)p;
     }
-    int64_t walk;
     // this iteration's Philox block of this lane (attempt gl, or the gate)
     Philox4 pb;
     // the gate words (block (t, 0, 1), drawn by lane G-1), broadcast to the
     // group as soon as they are drawn
     uint32_t gate[3];
+    // kFP: bit q: gate word q is below its threshold
+    uint32_t open;
     // zero-factor flags of the two terms of the last flip
     bool zfi, zfj;
     // this iteration is written to the training log
     bool logging;
-    int fmt_slot;
     // largest rank of the walks of this wavefront, rounded up to even: the
     // wave-uniform bound of the attempt-parallel match scan
     int scan_end;
@@ -362,7 +436,7 @@ struct Walker {
     }
     __device__ __forceinline__ Philox4 draw_at(uint64_t tt, uint32_t att, uint32_t dom) const
     {
-        uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+        uint32_t k0 = (uint32_t)seed(), k1 = (uint32_t)(seed() >> 32);
         asm volatile("" : "+v"(k0), "+v"(k1));
         return philox4x32_10((uint32_t)tt, (uint32_t)(tt >> 32), att, dom, k0, k1);
     }
@@ -601,6 +675,7 @@ struct Walker {
         if (tr0 == h) tr0 = -1;
         if (tr1 == h) tr1 = -1;
         fp_stale = true;
+        if constexpr (kClose) set_close(h, true);
         if constexpr (IX) {
             // drop bit h from every mask; bit `last` becomes bit h, and the
             // masks of term `last` move to slot h
@@ -717,7 +792,7 @@ struct Walker {
         }
         if (logging && gl == 0) {
             const KArgs &ra = rare();
-            tsf_flip_log *lg = ra.log + (size_t)walk * ra.log_cap + (t - 1);
+            tsf_flip_log *lg = ra.log + (size_t)walk() * ra.log_cap + (t - 1);
             const TV<T> fv[6] = {xi, yi, zi0, xj, yj, zj0};
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
@@ -781,8 +856,8 @@ struct Walker {
         st(i, Y, ny);
         st(j, Z, nz);
         if constexpr (kFP) {
-            set_fp(i, Y, fhash(ny, Y));
-            set_fp(j, Z, fhash(nz, Z));
+            const bool ni = set_fp(i, Y, fhash(ny, Y)), nj = set_fp(j, Z, fhash(nz, Z));
+            if constexpr (kClose) near = ni || nj;
         }
         wave_lds_sync();
     }
@@ -853,22 +928,51 @@ struct Walker {
     {
         asm volatile("; kind %0" ::"n"(X));
     }
-    // fingerprint of factor X of term k := h
+    // fingerprint of factor X of term k := h; returns whether a term had it
     template <int X>
-    __device__ __forceinline__ void set_fp_x(int k, uint32_t h)
+    __device__ __forceinline__ bool set_fp_x(int k, uint32_t h)
     {
+        uint32_t diff = ~0u;  // zero where a slot has it
 #pragma unroll
-        for (int q = 0; q < S; ++q) fp[q][X] = q * 64 + gl == k ? h : fp[q][X];
+        for (int q = 0; q < S; ++q) {
+            if constexpr (kClose) diff = min(diff, fp[q][X] ^ h);
+            fp[q][X] = q * 64 + gl == k ? h : fp[q][X];
+        }
+        const bool any = kClose && __ballot(diff == 0) != 0;
         keep_apart<X>();
+        return any;
     }
-    __device__ __forceinline__ void set_fp(int k, int X, uint32_t h)
+    __device__ __forceinline__ bool set_fp(int k, int X, uint32_t h)
     {
+        bool any;
         if (X == 0)
-            set_fp_x<0>(k, h);
+            any = set_fp_x<0>(k, h);
         else if (X == 1)
-            set_fp_x<1>(k, h);
+            any = set_fp_x<1>(k, h);
         else
-            set_fp_x<2>(k, h);
+            any = set_fp_x<2>(k, h);
+        return any;
+    }
+    // Terms that agree in two factors are looked for after every flip.  Terms that
+    // were found alone stay so until a flip gives one of them a fingerprint that
+    // another term has (two comparisons per slot when it is set), so the search,
+    // with the hashes of both terms and six comparisons per slot, is left out for
+    // pairs of such terms.  At the start of a call, and after a restart, every
+    // term counts as close until it is flipped.  8,192 (6,7,9) walks 14.2 -> 13.6 ms
+    // for 1,000 iterations, 1,777 (3,4,5) walks with expands 2.37 -> 2.13 us an
+    // iteration.
+    __device__ __forceinline__ uint32_t slot_bit(int k) const
+    {
+        return gl == (k & 63) ? 1u << (k >> 6) : 0u;
+    }
+    __device__ __forceinline__ bool may_be_close(int k) const
+    {
+        return (from_lane(close, k & 63) >> (k >> 6) & 1u) != 0;
+    }
+    __device__ __forceinline__ void set_close(int k, bool v)
+    {
+        const uint32_t b = slot_bit(k);
+        close = v ? close | b : close & ~b;
     }
     // this lane's slots (bit q) whose factor X has fingerprint h, without term
     // self.  With one or two slots all three kinds are compared: a hash that
@@ -989,17 +1093,17 @@ struct Walker {
             const int nb = T_ < G - 1 ? T_ : G - 1;  // attempt 63 is drawn below
             for (int e = 0; e < nb; ++e)
                 if (try_probe(p, dbase + e, c0, c1)) {
-                    cnt[C_ATTEMPTS] += (uint32_t)(e + 1);
+                    count(C_ATTEMPTS, (uint32_t)(e + 1));
                     return pick_probe(p, dbase + e, from_lane(pb.x[2], dbase + e), c0, c1);
                 }
         }
-        cnt[C_ATTEMPTS] += (uint32_t)T_;
+        count(C_ATTEMPTS, (uint32_t)T_);
         if (T_ == G) {
             const Philox4 w = draw((uint32_t)(G - 1), 0);
             const Probe p = probe((int)below(w.x[0], (uint32_t)r), (int)below(w.x[1], 3u));
             if (try_probe(p, 0, c0, c1)) return pick_probe(p, 0, from_lane(w.x[2], 0), c0, c1);
         }
-        cnt[C_FALLBACKS]++;
+        count(C_FALLBACKS, 1);
         const uint32_t f0 = from_lane(pb.x[3], dbase), f1 = from_lane(pb.x[3], dbase + 1);
         const int npairs = 3 * r;
         const int p0 = (int)below(f0, (uint32_t)npairs);
@@ -1026,7 +1130,13 @@ struct Walker {
         const uint32_t ca = ia < 0 ? 0u : two_shared_fp(h, 0, ia);
         const uint32_t cb = ib < 0 ? 0u : two_shared_fp(h, 3, ib);
         ka = kb = -1;
-        if (!__ballot((ca | cb) != 0)) return;  // the common case
+        const bool any_a = __ballot(ca != 0) != 0, any_b = __ballot(cb != 0) != 0;
+        if constexpr (kClose) {
+            close |= ca | cb;
+            if (ia >= 0) set_close(ia, any_a);
+            if (ib >= 0) set_close(ib, any_b);
+        }
+        if (!any_a && !any_b) return;  // the common case
         ka = first_merge_fp(ia, ca);
         kb = first_merge_fp(ib, cb);
     }
@@ -1037,6 +1147,15 @@ struct Walker {
         const uint32_t u = match_fp_x<0>(from_lane(h, l)), v = match_fp_x<1>(from_lane(h, l + 1)),
                        w = match_fp_x<2>(from_lane(h, l + 2));
         return drop_term((u & v) | (u & w) | (v & w), self);
+    }
+    // the terms close to term k, and whether it is
+    __device__ void find_close(int k)
+    {
+        refresh_fp();
+        const int X = gl % 3;
+        const uint32_t c = two_shared_fp(fhash(ld(k, X), X), 0, k);
+        close |= c;
+        set_close(k, __ballot(c != 0) != 0);
     }
     __device__ int first_merge_fp(int ti, uint32_t c) const
     {
@@ -1427,11 +1546,11 @@ struct Walker {
                         const int j = (role ? m1 : m0).kth(c);  // one search, on the chosen set
                         pick = pack_flip(i, j, X, role);
                     }
-                    cnt[C_ATTEMPTS] += (uint32_t)(base + win + 1);
+                    count(C_ATTEMPTS, (uint32_t)(base + win + 1));
                     return from_lane(pick, win);
                 }
             }
-            cnt[C_ATTEMPTS] += (uint32_t)T_;
+            count(C_ATTEMPTS, (uint32_t)T_);
             return fallback_ap();
         } else {
             TV<T> F[S][3];
@@ -1441,7 +1560,7 @@ struct Walker {
             for (int att = 0; att < T_; ++att) {
                 uint32_t w0, w1, w2;
                 attempt_words(att, w0, w1, w2);
-                cnt[C_ATTEMPTS]++;
+                count(C_ATTEMPTS, 1);
                 const int i = (int)below(w0, (uint32_t)r);
                 const int X = (int)below(w1, 3u);
                 candidates_tp(i, X, F, m0, m1, n0, n1);
@@ -1465,7 +1584,7 @@ struct Walker {
     // candidate U(w3 of (t,1,0), n).  None at all: a dead end.
     __device__ uint32_t fallback_tp(const TV<T> (&F)[S][3])
     {
-        cnt[C_FALLBACKS]++;
+        count(C_FALLBACKS, 1);
         uint64_t m0[S], m1[S];
         int n0, n1;
         const uint32_t f0 = from_lane(pb.x[3], 0), f1 = from_lane(pb.x[3], 1);
@@ -1491,7 +1610,7 @@ struct Walker {
     // first lane (in pair order) with a partner wins.
     __device__ uint32_t fallback_ap()
     {
-        cnt[C_FALLBACKS]++;
+        count(C_FALLBACKS, 1);
         const uint32_t f0 = from_lane(pb.x[3], 0), f1 = from_lane(pb.x[3], 1);
         const int npairs = 3 * r;
         const int p0 = (int)below(f0, (uint32_t)npairs);
@@ -1672,6 +1791,9 @@ struct Walker {
             const uint64_t cb = tr1 >= 0 ? two_shared(tr1) : 0ull;
             if ((ca | cb) == 0) return 0;
         }
+        if constexpr (kClose)
+            if (!near && !fp_stale && !may_be_close(tr0) && !may_be_close(tr1))
+                return 0;  // the common case
         bool done0 = tr0 < 0;
         for (;;) {
             const int ia = done0 ? -1 : tr0, ib = tr1;
@@ -1765,10 +1887,14 @@ struct Walker {
 #pragma unroll 1
                 for (int x = 0; x < 3; ++x) refresh_one(j, x, false);
             }
-            cnt[C_EXPANDS]++;
+            if constexpr (kClose) {
+#pragma unroll 1
+                for (int x = 0; x < 3; ++x) find_close(x == 0 ? i : x == 1 ? j : nw);
+            }
+            count(C_EXPANDS, 1);
             return true;
         }
-        cnt[C_EXPAND_FAILS]++;
+        count(C_EXPAND_FAILS, 1);
         return false;
     }
 
@@ -1778,6 +1904,7 @@ struct Walker {
     __device__ void load_scheme(const uint64_t *src, int rr)
     {
         fp_stale = true;
+        if constexpr (kClose) close = ~0u;
         for (int k = gl; k < rr; k += G)
 #pragma unroll
             for (int X = 0; X < 3; ++X) {
@@ -1834,7 +1961,7 @@ struct Walker {
     // non-zero coefficients - 2r - mp, Sec. 4.5) at most the target
     __device__ __forceinline__ bool reached() const
     {
-        return additions ? best_nnz - 2 * best_rank - mp <= target : best_rank <= target;
+        return additions ? best_nnz() - 2 * best_rank - mp() <= target() : best_rank <= target();
     }
 
     __device__ void restart_check()
@@ -1843,29 +1970,28 @@ struct Walker {
             const KArgs &ra = rare();
             const bool from_best = ra.restart_from_best != 0;
             const uint64_t *src = (from_best ? (const uint64_t *)ra.best : ra.start) +
-                                  (size_t)walk * ra.cap * 6;
-            const int rr = from_best ? best_rank : start_rank;
+                                  (size_t)walk() * ra.cap * 6;
+            const int rr = from_best ? best_rank : start_rank();
             load_scheme(src, rr);
             r = rr;
             if (additions) nnz = count_nnz();
             start_plateau();
-            cnt[C_RESTARTS]++;
+            count(C_RESTARTS, 1);
         }
     }
     __device__ __forceinline__ void start_plateau()
     {
-        plateau_start = t;
+        set_plateau_start(t);
         set_restart();
     }
     __device__ __forceinline__ void set_restart()
     {
         const int64_t pl = rare().plateau, never = INT64_MAX;
-        restart_at = pl <= 0 || pl > never - plateau_start ? never : plateau_start + pl;
+        restart_at = pl <= 0 || pl > never - plateau_start() ? never : plateau_start() + pl;
     }
 
     __device__ void begin_iteration()
     {
-        int gate_from = G - 1;
         if constexpr (kFP) {
             // one draw serves 64 >> dsh iterations: the blocks depend on the
             // iteration number alone, and an iteration needs few of the lanes
@@ -1873,16 +1999,23 @@ struct Walker {
                 const uint32_t att = (uint32_t)gl & ((1u << dsh) - 1u);
                 const bool gates = att == (1u << dsh) - 1u;
                 pb = draw_at((uint64_t)t + (uint64_t)(gl >> dsh), gates ? 0u : att, gates ? 1u : 0u);
+                // the gates' lanes compare their words at once, and keep the
+                // outcome in the word that no gate uses
+                const KArgs &ra = rare();
+                const uint32_t o = ((uint64_t)pb.x[0] < ra.t_eq ? 1u : 0u) |
+                                   ((uint64_t)pb.x[1] < ra.t_reduce ? 2u : 0u) |
+                                   ((uint64_t)pb.x[2] < ra.t_expand ? 4u : 0u);
+                pb.x[3] = gates ? o : pb.x[3];
                 dbase = 0;
             }
-            gate_from = dbase + (1 << dsh) - 1;
+            open = from_lane(pb.x[3], dbase + (1 << dsh) - 1);
         } else {
             // this iteration's draws: lane q < G-1 -> flip attempt q, lane G-1 -> gates
             const bool gate_lane = gl == G - 1;
             pb = draw(gate_lane ? 0u : (uint32_t)gl, gate_lane ? 1u : 0u);
-        }
 #pragma unroll
-        for (int q = 0; q < 3; ++q) gate[q] = from_lane(pb.x[q], gate_from);
+            for (int q = 0; q < 3; ++q) gate[q] = from_lane(pb.x[q], G - 1);
+        }
         logging = t <= log_until;
     }
 
@@ -1895,17 +2028,19 @@ struct Walker {
         if (!found) {
             // Algorithm 1: no flip -> expand, continue (the additions
             // objective keeps the rank and does not expand)
-            cnt[C_DEAD_ENDS]++;
+            count(C_DEAD_ENDS, 1);
             grow = !additions;
         } else {
             int tr0 = fi, tr1 = fj;
             // gates: block (t, 0, 1), drawn by the last lane of the group
-            const uint32_t g0 = gate[0];
+            const auto passes = [&](int q, uint64_t limit) {
+                return kFP ? (open >> q & 1u) != 0 : (uint64_t)gate[q] < limit;
+            };
             if (additions) {
                 // the rank is unchanged: best by non-zero count, no reduce or
                 // expand
-                improved = nnz < best_nnz;
-                accepted = !improved && nnz == best_nnz && (uint64_t)g0 < a->t_eq;
+                improved = nnz < best_nnz();
+                accepted = !improved && nnz == best_nnz() && passes(0, a->t_eq);
             } else {
                 // terms with a zero factor go, the higher index first
                 const bool zi = zfi, zj = zfj;
@@ -1913,40 +2048,41 @@ struct Walker {
                 const int h2 = zi && zj ? (fi > fj ? fj : fi) : -1;
                 if (h1 >= 0) {
                     swap_remove(h1, tr0, tr1);
-                    cnt[C_ZERO_REMOVED]++;
+                    count(C_ZERO_REMOVED, 1);
                 }
                 if (h2 >= 0) {
                     swap_remove(h2, tr0, tr1);
-                    cnt[C_ZERO_REMOVED]++;
+                    count(C_ZERO_REMOVED, 1);
                 }
                 improved = r < best_rank;
-                accepted = !improved && r == best_rank && (uint64_t)g0 < a->t_eq;
+                accepted = !improved && r == best_rank && passes(0, a->t_eq);
             }
             if (improved || accepted) {
                 const KArgs &ra = rare();
-                const int c = store_scheme(ra.best + (size_t)walk * ra.cap * 6);
-                best_nnz = additions ? nnz : c;
+                const int c = store_scheme(ra.best + (size_t)walk() * ra.cap * 6);
+                set_best_nnz(additions ? nnz : c);
                 best_rank = r;
-                cnt[C_IMPROVEMENTS] += improved ? 1u : 0u;
-                cnt[C_EQ_ACCEPTS] += improved ? 0u : 1u;
+                count(C_IMPROVEMENTS, improved ? 1u : 0u);
+                count(C_EQ_ACCEPTS, improved ? 0u : 1u);
             }
             if (improved) {
                 start_plateau();
                 hit = reached();
                 const KArgs &ra = rare();
-                if (gl == 0 && n_rec < ra.rec_cap) {
-                    tsf_record *rc = ra.rec + (size_t)walk * ra.rec_cap + n_rec;
+                if (gl == 0 && n_rec() < ra.rec_cap) {
+                    tsf_record *rc = ra.rec + (size_t)walk() * ra.rec_cap + n_rec();
                     rc->iter = t;
-                    rc->rank = additions ? nnz - 2 * r - mp : r;
+                    rc->rank = additions ? nnz - 2 * r - mp() : r;
                     rc->reserved = 0;
                 }
-                n_rec++;
+                set_n_rec(n_rec() + 1);
             }
             if (!additions) {
-                const uint32_t g1 = gate[1];
-                const uint32_t g2 = gate[2];
-                if ((uint64_t)g1 < a->t_reduce) cnt[C_MERGES] += (uint32_t)reduce(tr0, tr1);
-                grow = (uint64_t)g2 < a->t_expand && r <= best_rank + 2 && r < r_cap;
+                if (passes(1, a->t_reduce))
+                    count(C_MERGES, (uint32_t)reduce(tr0, tr1));
+                else if constexpr (kClose)
+                    close = near ? ~0u : close;
+                grow = passes(2, a->t_expand) && r <= best_rank + 2 && r < r_cap;
             }
         }
         if (grow) expand();
@@ -1958,14 +2094,14 @@ struct Walker {
     {
         if (logging && gl == 0) {
             const KArgs &ra = rare();
-            tsf_flip_log *lg = ra.log + (size_t)walk * ra.log_cap + (t - 1);
+            tsf_flip_log *lg = ra.log + (size_t)walk() * ra.log_cap + (t - 1);
             lg->iter = t;
             if (!flipped) {
                 lg->rank_before = -1;
                 for (int q = 0; q < 12; ++q) lg->f[q] = 0;
             }
             lg->rank_after = r;
-            lg->format_slot = fmt_slot;
+            lg->format_slot = fmt_slot();
             lg->reserved = 0;
             lg->pad = 0;
         }
@@ -1978,12 +2114,13 @@ struct Walker {
     // (and none in Z2) and no entry beyond the factor's length
     // (TSF_CHECK_CODING); u and v of every live term normalised, Sec. 3.6
     // (TSF_CHECK_NORMALISED); IX: every mask equal to the relation it
-    // indexes, FP: every fingerprint that of its factor (TSF_CHECK_INDEX); PK: slots at or above the rank dead
-    // (TSF_CHECK_DEAD_SLOTS).  Returns the OR of the failed checks.
+    // indexes, FP: every fingerprint that of its factor, and no term close to
+    // another that is said not to be (TSF_CHECK_INDEX); PK: slots at or above
+    // the rank dead (TSF_CHECK_DEAD_SLOTS).  Returns the OR of the failed checks.
     __device__ uint32_t check_state(const int (&len)[3]) const
     {
         uint32_t bad = 0;
-        if (r < 1 || r > r_cap || best_rank > start_rank) bad |= TSF_CHECK_RANK;
+        if (r < 1 || r > r_cap || best_rank > start_rank()) bad |= TSF_CHECK_RANK;
         // terms below the rank, never beyond the capacity (the mask rows)
         const int rr = r < 0 ? 0 : (r > a->cap ? a->cap : r);
         for (int k = gl; k < rr; k += G) {
@@ -2019,6 +2156,15 @@ struct Walker {
                     for (int X = 0; X < 3; ++X)
                         if (fp[q][X] != (k < rr ? fhash(f[X], X) : 0u)) bad |= TSF_CHECK_INDEX;
                 }
+            if (kClose && !additions)
+                for (int k = gl; k < rr; k += G)
+                    for (int j = 0; j < rr; ++j) {
+                        if (j == k || (close >> (k >> 6) & 1u)) continue;
+                        int same = 0;
+#pragma unroll
+                        for (int X = 0; X < 3; ++X) same += equiv(ld(j, X), ld(k, X), X) ? 1 : 0;
+                        if (same >= 2) bad |= TSF_CHECK_INDEX;
+                    }
         }
         uint32_t all = 0;
 #pragma unroll
@@ -2080,15 +2226,15 @@ struct Walker {
         wave_lds_sync();
         for (uint64_t live = gballot(desc != ~0u); live; live &= live - 1) {
             const int row = __builtin_ctzll(live);
-            uint16_t *out = a->feat + ((size_t)walk * kLearnRows + row) * 512;
+            uint16_t *out = a->feat + ((size_t)walk() * kLearnRows + row) * 512;
 #pragma unroll
             for (int e = gl; e < 64; e += G) {
                 const int blk = e < 48 ? e >> 3 : 0;
                 store_feature_piece(out, e, feature_piece(e, rows[12 * row + 2 * blk],
-                                                          rows[12 * row + 2 * blk + 1], fmt_slot, r));
+                                                          rows[12 * row + 2 * blk + 1], fmt_slot(), r));
             }
         }
-        if (gl < kLearnRows) a->cand[(size_t)walk * kLearnRows + gl] = desc;
+        if (gl < kLearnRows) a->cand[(size_t)walk() * kLearnRows + gl] = desc;
     }
 
     // Phase 2: apply the best-scored candidate (ties: the lower attempt), or
@@ -2100,15 +2246,15 @@ struct Walker {
         uint32_t desc = ~0u;
         float score = -__builtin_inff();
         if (gl < K) {
-            desc = a->cand[(size_t)walk * kLearnRows + gl];
-            const float l = a->logit[(size_t)walk * kLearnRows + gl];
+            desc = a->cand[(size_t)walk() * kLearnRows + gl];
+            const float l = a->logit[(size_t)walk() * kLearnRows + gl];
             if (desc != ~0u) score = (l == l) ? l : -__builtin_inff();
         }
         const bool valid = desc != ~0u;
         float best = score;
         for (int off = 1; off < G; off <<= 1) best = fmaxf(best, __shfl_xor(best, off, G));
         const uint64_t win_mask = gballot(valid && score == best);
-        cnt[C_ATTEMPTS] += (uint32_t)K;
+        count(C_ATTEMPTS, (uint32_t)K);
         int fi = -1, fj = -1;
         uint32_t d = kNoFlip;
         uint8_t choice = 255;
@@ -2124,7 +2270,7 @@ struct Walker {
         const bool found = d != kNoFlip;
         if (found) apply_packed(d, fi, fj);
         if (a->choice && gl == 0 && t <= a->choice_cap)
-            a->choice[(size_t)walk * a->choice_cap + (t - 1)] = choice;
+            a->choice[(size_t)walk() * a->choice_cap + (t - 1)] = choice;
         finish_iteration(found, fi, fj);
     }
 };
@@ -2192,7 +2338,9 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     wk.mk = reinterpret_cast<uint64_t *>(smem + (size_t)wpb * W * a.cap2 * 3 * Wk::kFW) +
             (size_t)slot * (LRN ? 12 * kLearnRows : a.capm * 3);
     wk.a = &a;
-    wk.walk = walk;
+#pragma unroll
+    for (int k = 0; k < (Wk::kFP ? 1 : (int)Wk::K_NUM); ++k) wk.kept[k] = 0;
+    wk.put64(Wk::K_WALK, (uint64_t)walk);
     tsf_walk_header *h = a.hdr + walk;
     const int m = h->m, n = h->n, p = h->p;
     int done = h->done;
@@ -2213,27 +2361,25 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
         if (wk.gl == 0) h->done = -3;
         return;
     }
-    wk.seed = a.base_seed + (uint64_t)(a.first_walk_id + walk);
+    wk.put64(Wk::K_SEED, a.base_seed + (uint64_t)(a.first_walk_id + walk));
     wk.r = h->rank;
     wk.r_cap = h->r_cap;
     wk.best_rank = h->best_rank;
-    wk.best_nnz = h->best_nnz;
-    wk.mp = m * p;
-    wk.target = h->target_rank;
+    wk.set_best_nnz(h->best_nnz);
+    wk.put(Wk::K_MP, (uint32_t)(m * p));
+    wk.put(Wk::K_TARGET, (uint32_t)h->target_rank);
     wk.additions = a.objective == TSF_OBJ_ADDITIONS;
     wk.nnz = 0;
-    wk.start_rank = h->start_rank;
-    wk.n_rec = h->n_rec;
+    wk.put(Wk::K_START_RANK, (uint32_t)h->start_rank);
+    wk.set_n_rec(h->n_rec);
     wk.t = h->t;
     const uint32_t t_first = (uint32_t)wk.t;
-    wk.plateau_start = h->plateau_start;
+    wk.set_plateau_start(h->plateau_start);
     wk.set_restart();
     wk.log_until = a.log != nullptr ? a.log_cap : 0;
     wk.hit = wk.reached();
-#pragma unroll
-    for (int c = 0; c < C_NUM; ++c) wk.cnt[c] = 0;
     wk.logging = false;
-    wk.fmt_slot = format_slot(m, n, p);
+    wk.put(Wk::K_FMT_SLOT, (uint32_t)format_slot(m, n, p));
     wk.load_scheme(a.cur + (size_t)walk * a.cap * 6, wk.r);
     if (wk.additions) wk.nnz = wk.count_nnz();
     uint64_t err = 0;
@@ -2295,17 +2441,24 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
         h = ra.hdr + walk;
         h->rank = wk.r;
         h->best_rank = wk.best_rank;
-        h->best_nnz = wk.best_nnz;
+        h->best_nnz = wk.best_nnz();
         h->done = done;
-        h->n_rec = wk.n_rec;
+        h->n_rec = wk.n_rec();
         h->t = wk.t;
-        h->plateau_start = wk.plateau_start;
+        h->plateau_start = wk.plateau_start();
         h->params_hash = ra.params_hash;
         if (CHK && done == -4) h->reserved = err;
-        // every iteration of this call is a flip or a dead end
-        wk.cnt[C_ITERS] = (uint32_t)wk.t - t_first;
-        wk.cnt[C_FLIPS] = wk.cnt[C_ITERS] - wk.cnt[C_DEAD_ENDS];
-        for (int c = 0; c < C_NUM; ++c) h->counters[c] += wk.cnt[c];
+    }
+    // every iteration of this call is a flip or a dead end
+    const uint32_t iters = (uint32_t)wk.t - t_first;
+    wk.count(C_ITERS, iters);
+    wk.count(C_FLIPS, iters - wk.get(Wk::K_CNT + C_DEAD_ENDS));
+    if constexpr (Wk::kFP) {
+        const int c = lane - Wk::K_CNT;
+        if (c >= 0 && c < C_NUM) (ra.hdr + walk)->counters[c] += wk.kept[0];
+    } else if (wk.gl == 0) {
+#pragma unroll
+        for (int c = 0; c < C_NUM; ++c) h->counters[c] += wk.kept[Wk::K_CNT + c];
     }
 }
 
@@ -2314,12 +2467,17 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
 // allows at (3,3,3) (10,176 bytes per 8-walk wavefront, sixteen per CU); the
 // other indexed kernels with 32-bit masks to 168 VGPRs (three per SIMD, as
 // many as their LDS allows), the plain attempt-parallel ones with 32-bit masks
-// to 128 (four per SIMD, as 88 terms at 16 lanes leave room for); the rest are
-// not constrained (the term-parallel kernels with 64 lanes need 74 to 130).
+// to 128 (four per SIMD, as 88 terms at 16 lanes leave room for), and one walk
+// per wavefront with 64-bit masks and up to 128 terms to 80 (six per SIMD, as
+// many as the LDS of 128 terms allows, although 15 registers go to scratch: a
+// round of 16,384 exploratory walks 6.90 ms at four per SIMD, 6.33 at five, 5.51
+// at six); the rest are not constrained (the term-parallel kernels with 64
+// lanes need 70 to 137).
 template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK = false>
 __global__ void __launch_bounds__(256) __attribute__((
     amdgpu_waves_per_eu((PK || (AP && !IX && sizeof(T) == 4)) && G >= 8 ? 4
                         : (IX && G >= 8 && sizeof(T) == 4)               ? 3
+                        : (!AP && G == 64 && S == 2 && sizeof(T) == 8)   ? 6
                                                                          : 1)))
 walk_kernel(KArgs a)
 {
