@@ -8,6 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("cap,walks", [
+    (32, 1024), (33, 1024), (33, 1025), (41, 3072), (41, 3073), (65, 12288), (65, 12289),
     (40, 1024), (41, 1024), (41, 1025), (48, 4096), (48, 4097), (48, 8193), (49, 8193),
     (64, 33), (65, 33), (65, 8192), (65, 8193), (72, 16385), (73, 16385), (96, 8193),
     (97, 8193), (128, 17)])
