@@ -371,16 +371,20 @@ struct Walker {
             kept[K_CNT + c] += n;
     }
     const KArgs *a;
-    // the arguments (the kernel's only one, so at the start of its argument
-    // segment) for code that seldom runs: read from memory there, where the
-    // compiler would otherwise keep them all in scalar registers for the whole
-    // kernel and spill those into lanes of vector registers
-    __device__ __forceinline__ static const KArgs &rare()
+    // The arguments (the kernel's only one, so at the start of its argument
+    // segment) for code that seldom runs: read from memory there, at an offset
+    // that the compiler does not know to be 0, where it would otherwise keep
+    // them all in scalar registers for the whole kernel and spill those into
+    // lanes of vector registers.  walk_body, which is part of the kernel itself,
+    // takes the segment's address: in a function that is called it would be null.
+    typedef const __attribute__((address_space(4))) char *ArgsPtr;
+    ArgsPtr args;
+    __device__ __forceinline__ const KArgs &rare() const
     {
+        uint32_t off = 0;
+        asm volatile("" : "+s"(off));
         typedef const __attribute__((address_space(4))) KArgs *Const;
-        Const p = (Const)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(p));
-        return *(const KArgs *)p;
+        return *(const KArgs *)(Const)(args + off);
     }
     // this iteration's Philox block of this lane (attempt gl, or the gate)
     Philox4 pb;
@@ -2338,6 +2342,7 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
     wk.mk = reinterpret_cast<uint64_t *>(smem + (size_t)wpb * W * a.cap2 * 3 * Wk::kFW) +
             (size_t)slot * (LRN ? 12 * kLearnRows : a.capm * 3);
     wk.a = &a;
+    wk.args = (typename Wk::ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
 #pragma unroll
     for (int k = 0; k < (Wk::kFP ? 1 : (int)Wk::K_NUM); ++k) wk.kept[k] = 0;
     wk.put64(Wk::K_WALK, (uint64_t)walk);
