@@ -3,6 +3,7 @@
 // (walk_kernel.h, instantiated in walk_inst.hip).
 #include "walk_kernel.h"
 #include "tsf_internal.h"
+#include "tsf_launch.h"
 #include "tsf_meta.h"
 
 #include <cstring>
@@ -956,43 +957,6 @@ struct Launch {
     bool ap, ix;
 };
 
-// The strategy and lanes per walk of a call that names neither.  Times are us
-// per iteration of the whole batch, rank objective, ternary.
-//  * Small batches do not fill the 1,024 SIMDs, and an iteration's latency
-//    counts: the fewer walks share a wavefront, the less each waits for the
-//    others' branches.  Up to 4,096 walks 32 lanes each ((2,2,2), 256 walks:
-//    2.1 with 32 lanes, 2.3 with 8), up to 8,192 walks 16 lanes (capacity 58:
-//    3.0 against 3.5); one wavefront per walk with fingerprints where the
-//    indexed kernels' masks are long and no SIMD has more than three wavefronts
-//    (capacity 58, 1,024 walks: 2.1 against 2.5 with 32 lanes; 3,072 walks 2.5
-//    against 2.7; 4,096 walks 2.8 against 2.7), or one, from 33 terms (capacity
-//    35, 1,024 walks: 2.0 against 2.1; 26: 2.2 against 2.1).
-//  * Beyond 64 terms the indexed kernels end and the attempts of the
-//    attempt-parallel ones scan every term: one wavefront per walk is faster
-//    until the chip is full (capacity 88: 4,096 walks 2.9 against 7.1 with 16
-//    lanes, 12,288 walks 7.0 against 9.4, 32,768 walks 19.2 against 18.3; at
-//    16,384 walks both take 9.5, but with fewer terms in the walks, as in
-//    batches of several formats, only the scans become shorter), and always
-//    above 96 terms, where their partner scans and LDS grow (capacity 108,
-//    65,536 walks: 37 against 49).
-//  * Full chips: 8 lanes, or 16 where a walk's LDS leaves a CU too few
-//    wavefronts of eight walks (capacity 56, 65,536 walks: 14.3 against 15.0;
-//    capacity 88: 36.5 against 38.9; capacity 44: 13.4 against 11.4).
-tsf_launch default_launch(const tsf_walk_params *prm, const tsf_walk_batch *b)
-{
-    const bool wide = b->max_len > 32;
-    const int cap = b->capacity, n = b->n_walks;
-    if (cap <= 64) {
-        if (!wide && cap > 32 && n <= (cap > 40 ? 3072 : 1024)) return tsf_launch{64, 0, 2};
-        const int lanes = n <= 4096 ? 32 : n <= 8192 || wide || cap > 48 ? 16 : 8;
-        return tsf_launch{lanes, 0, 3};
-    }
-    if (wide || cap > 96 || n <= 12288) return tsf_launch{64, 0, 2};
-    const bool sixteen =
-        n <= 16384 || (prm->objective == TSF_OBJ_RANK && (cap > 72 || n <= 40960));
-    return tsf_launch{sixteen ? 16 : 8, 0, 1};
-}
-
 // validate a walk call and build its kernel arguments and launch shape
 tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int64_t n_iters,
                         const tsf_launch *launch, KArgs &a, Launch &L, bool checked = false,
@@ -1050,15 +1014,9 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
                         ap ? 8 : 64);
     L.fn = pick_kernel(g, s, wide, b->mode == TSF_Z2, learned ? 5 : pk ? 4 : strategy, checked);
     if (!L.fn) return tsf_fail(TSF_E_ARG, "no kernel for this configuration");
-    const size_t word = wide ? 8 : 4;
-    const size_t factor_bytes = pk ? 4 : 2 * word;
     const int walks_per_wave = 64 / g;
-    // LDS stride per factor kind: capacity rounded up to even (to a multiple
-    // of 4 for the indexed strategy, which reads four terms at a time)
-    const int cap2 = ix ? (b->capacity + 3) & ~3 : b->capacity + (b->capacity & 1);
-    // per walk: the terms, and for the indexed strategy 3 match masks per term
-    // (rows of `capacity` masks, not padded)
-    const size_t per_walk = (size_t)cap2 * 3 * factor_bytes + (ix ? (size_t)b->capacity * 3 * 8 : 0);
+    const int cap2 = lds_stride(b->capacity, ix);
+    const size_t per_walk = walk_lds(b->capacity, b->max_len, ix);
     L.lds = (size_t)wpb * walks_per_wave * per_walk;
     if (L.lds > 160 * 1024)
         return tsf_fail(TSF_E_CAPACITY, "%zu bytes of LDS per workgroup exceed 160 KiB", L.lds);
