@@ -345,11 +345,13 @@ typedef struct tsf_ctx tsf_ctx;
 tsf_status tsf_ctx_create(tsf_ctx **ctx);
 tsf_status tsf_ctx_destroy(tsf_ctx *ctx);
 
-/* Autotuner: time every launch configuration that fits the batch (strategy,
- * lanes per walk, wavefronts per workgroup) for trial_iters iterations on a
- * private copy of the batch's state -- the batch itself is not changed -- and
- * remember the fastest for batches of the same capacity, max_len, mode and
- * size class; later tsf_walk calls with launch == NULL (or all fields 0) use
+/* Autotuner: time the launch that a call without tuning takes and others that
+ * fit the batch (4, 8 and 16 lanes per walk of strategies 3 and 1, 16, 32 and
+ * 64 of strategy 2; 1, 2 and 4 wavefronts per workgroup) for trial_iters
+ * iterations on a private copy of the batch's state -- the batch itself is not
+ * changed -- and remember the fastest for batches of the same capacity,
+ * max_len, mode and size class that are walked with the same objective; later
+ * tsf_walk calls with launch == NULL (or all fields 0) use
  * it.  The choice is also written to *chosen (may be NULL).  Results of walks
  * never depend on the configuration.  Synchronous.  The copy is allocated
  * inside the context and kept until tsf_ctx_destroy.

@@ -1,9 +1,10 @@
 // tsf_launch.h -- the strategy and lanes per walk of a walk call that leaves them
-// open (host code, no HIP).
+// open, and what the autotuner tries and remembers (host code, no HIP).
 #pragma once
 #include "../../include/tsf.h"
 
 #include <stddef.h>
+#include <vector>
 
 // LDS stride per factor kind: capacity rounded up to even (to a multiple of 4 for
 // the indexed strategy, which reads four terms at a time).
@@ -78,4 +79,55 @@ inline tsf_launch default_launch(const tsf_walk_params *prm, const tsf_walk_batc
     const bool sixteen = (ix ? wide || cap > 48 : rank || (cap % 16 == 0 && n <= 16384)) &&
                          launch_rounds(n, 16, lds) <= launch_rounds(n, 8, lds);
     return tsf_launch{sixteen ? 16 : 8, 0, ix ? 3 : 1};
+}
+
+// What tsf_autotune times: 4 to 16 lanes of the attempt-parallel strategies, 16 to
+// 64 of the term-parallel one and the launch that a call without tuning takes, so
+// that tuning never ends with a slower one; 1, 2 and 4 wavefronts per workgroup.
+inline std::vector<tsf_launch> tune_candidates(const tsf_walk_params *prm, const tsf_walk_batch *b)
+{
+    const tsf_launch d = default_launch(prm, b);
+    std::vector<tsf_launch> c;
+    for (int wpb : {1, 2, 4}) {
+        const auto add = [&](int lanes, int strategy) {
+            if (lanes != d.lanes_per_walk || strategy != d.strategy)
+                c.push_back(tsf_launch{lanes, wpb, strategy});
+        };
+        for (int st : {3, 1})
+            if (b->capacity <= (st == 3 ? 64 : 128))
+                for (int g : {4, 8, 16}) add(g, st);
+        for (int g : {16, 32, 64}) add(g, 2);
+        c.push_back(tsf_launch{d.lanes_per_walk, wpb, d.strategy});
+    }
+    return c;
+}
+
+// A tuned launch and the batches that it serves.
+struct TuneEntry {
+    int32_t capacity, max_len, mode, objective, size_class;
+    tsf_launch launch;
+    bool used;
+};
+
+inline int size_class(int n_walks)
+{
+    int c = 0;
+    while (n_walks > 1 && c < 30) {
+        n_walks >>= 1;
+        ++c;
+    }
+    return c;
+}
+
+inline TuneEntry tune_entry(const tsf_walk_params *prm, const tsf_walk_batch *b,
+                            const tsf_launch &launch)
+{
+    return TuneEntry{b->capacity,    b->max_len, b->mode, prm->objective, size_class(b->n_walks),
+                     launch, true};
+}
+
+inline bool tune_serves(const TuneEntry &e, const tsf_walk_params *prm, const tsf_walk_batch *b)
+{
+    return e.used && e.capacity == b->capacity && e.max_len == b->max_len && e.mode == b->mode &&
+           e.objective == prm->objective && e.size_class == size_class(b->n_walks);
 }

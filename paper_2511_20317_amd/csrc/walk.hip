@@ -795,13 +795,6 @@ struct GraphEntry {
     bool used;
 };
 
-// A tuned launch configuration for batches of one shape.
-struct TuneEntry {
-    int32_t capacity, max_len, mode, size_class;
-    tsf_launch launch;
-    bool used;
-};
-
 struct tsf_ctx {
     int device;
     int cu_count;
@@ -815,24 +808,12 @@ struct tsf_ctx {
 };
 
 namespace {
-int size_class(int n_walks)
+const tsf_launch *tuned_launch(const tsf_ctx *ctx, const tsf_walk_params *prm,
+                               const tsf_walk_batch *b)
 {
-    int c = 0;
-    while (n_walks > 1 && c < 30) {
-        n_walks >>= 1;
-        ++c;
-    }
-    return c;
-}
-
-const tsf_launch *tuned_launch(const tsf_ctx *ctx, const tsf_walk_batch *b)
-{
-    if (!ctx) return nullptr;
-    const int sc = size_class(b->n_walks);
+    if (!ctx || !prm) return nullptr;
     for (const TuneEntry &e : ctx->tuned)
-        if (e.used && e.capacity == b->capacity && e.max_len == b->max_len && e.mode == b->mode &&
-            e.size_class == sc)
-            return &e.launch;
+        if (tune_serves(e, prm, b)) return &e.launch;
     return nullptr;
 }
 
@@ -1077,7 +1058,7 @@ tsf_status tsf_walk(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_walk_bat
                     int64_t n_iters, const tsf_launch *launch, void *hip_stream)
 {
     if (launch_is_default(launch) && b) {
-        const tsf_launch *t = tuned_launch(ctx, b);
+        const tsf_launch *t = tuned_launch(ctx, prm, b);
         if (t) launch = t;
     }
     KArgs a;
@@ -1141,19 +1122,12 @@ tsf_status tsf_autotune(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_walk
               hipMemcpyAsync(bs.cur, b->cur, sz_sch, hipMemcpyDeviceToDevice, s) == hipSuccess &&
               hipMemcpyAsync(bs.best, b->best, sz_sch, hipMemcpyDeviceToDevice, s) == hipSuccess;
     if (!ok) return tsf_fail(TSF_E_DEVICE, "autotuner snapshot failed");
-    std::vector<tsf_launch> cands;
-    for (int wpb : {1, 2, 4}) {
-        for (int st : {3, 1})
-            if (b->capacity <= (st == 3 ? 64 : 128))
-                for (int g : {4, 8, 16}) cands.push_back(tsf_launch{g, wpb, st});
-        for (int g : {16, 32, 64}) cands.push_back(tsf_launch{g, wpb, 2});
-    }
     hipEvent_t e0, e1;
     hipEventCreate(&e0);
     hipEventCreate(&e1);
     float best_ms = -1.0f;
     tsf_launch best{0, 0, 0};
-    for (const tsf_launch &c : cands) {
+    for (const tsf_launch &c : tune_candidates(prm, b)) {
         KArgs a;
         Launch L;
         if (prepare_walk(prm, &bt, trial_iters, &c, a, L) != TSF_OK) continue;
@@ -1175,16 +1149,13 @@ tsf_status tsf_autotune(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_walk
     hipEventDestroy(e1);
     if (best_ms < 0.0f) return tsf_fail(TSF_E_CAPACITY, "no launch configuration fits the batch");
     TuneEntry *slot = nullptr;
-    const int sc = size_class(b->n_walks);
     for (TuneEntry &e : ctx->tuned)
-        if (e.used && e.capacity == b->capacity && e.max_len == b->max_len && e.mode == b->mode &&
-            e.size_class == sc)
-            slot = &e;
+        if (tune_serves(e, prm, b)) slot = &e;
     if (!slot) {
         slot = &ctx->tuned[ctx->next_tuned];
         ctx->next_tuned = (ctx->next_tuned + 1) % 16;
     }
-    *slot = TuneEntry{b->capacity, b->max_len, b->mode, sc, best, true};
+    *slot = tune_entry(prm, b, best);
     if (chosen) *chosen = best;
     return TSF_OK;
 }

@@ -48,3 +48,25 @@ def test_choice_near_its_bounds(fmt, cap, walks, terms, mode, wide, objective):
         assert torch.equal(x * live, y * live)
     some = {0, walks // 2, walks - 1, int(ranks[0].argmax())}
     compare(a, run_oracle(groups, prm, sorted(some), 40, splits=[29, 11]), "choice")
+
+
+def test_tuning_a_batch_whose_default_has_32_lanes():
+    """the tuned launch is one of the autotuner's, 32 lanes among them, the batch is left as
+    it was, and both objectives walk on from it as the oracle does"""
+    import torch
+    ctx = tsf.Context()
+    groups = [(tsf.init_scheme(2, 2, 2), 200, 16, -10 ** 6)]
+    for objective in (tsf.OBJ_RANK, tsf.OBJ_ADDITIONS):
+        prm = tsf.walk_params(base_seed=77, max_iters=500, plateau=200, objective=objective)
+        b = tsf.WalkBatch(groups, rec_cap=8)
+        b.init(ctx)
+        b.walk(ctx, prm, 100)
+        torch.cuda.synchronize()
+        before = (b.hdr.clone(), b.cur.clone(), b.best.clone())
+        lanes, waves, strategy = b.autotune(ctx, prm, trial_iters=100)
+        assert waves in (1, 2, 4) and (lanes in (4, 8, 16, 32) if strategy != 2 else
+                                       lanes in (16, 32, 64))
+        assert all(torch.equal(x, y) for x, y in zip(before, (b.hdr, b.cur, b.best)))
+        b.walk(ctx, prm, 400)
+        torch.cuda.synchronize()
+        compare(b, run_oracle(groups, prm, range(0, 200, 13), 500), "tuned")

@@ -39,3 +39,27 @@ def test_full_chips_take_no_round_more_than_needed(shim, max_len, objective):
             other = 24 - lanes
             assert (rounds(walks, lanes, cap, max_len, cap <= 64) <=
                     rounds(walks, other, cap, max_len, cap <= 64)), (cap, walks, lanes)
+
+
+def test_autotuner_times_the_default(shim):
+    """every launch once, and the one that a call without tuning takes among them"""
+    out = (C.c_int * 64)()
+    for cap in (1, 12, 35, 41, 49, 64, 65, 72, 88, 96, 97, 128, 129, 512):
+        for walks in (1, 256, 1024, 3073, 4096, 4097, 8192, 8193, 18432, 65536):
+            for max_len in (9, 32, 64):
+                for objective in (0, 1):
+                    n = shim.shim_candidates(cap, max_len, walks, objective, out, 64)
+                    got = list(out[:n])
+                    assert len(set(got)) == n <= 64
+                    strategy, lanes = divmod(shim.shim_default(cap, max_len, walks, objective), 100)
+                    for waves in (1, 2, 4):
+                        assert 1000 * strategy + 10 * lanes + waves in got
+
+
+def test_tuned_launch_serves_its_kind_of_batch_alone(shim):
+    def serves(a, b):
+        return shim.shim_serves((C.c_int * 5)(*a), (C.c_int * 5)(*b))
+    tuned = [88, 20, 20480, 0, 0]      # capacity, max_len, walks, objective, mode
+    assert serves(tuned, tuned) and serves(tuned, [88, 20, 17000, 0, 0])
+    for k, other in enumerate((87, 16, 32768, 1, 1)):
+        assert not serves(tuned, tuned[:k] + [other] + tuned[k + 1:])
