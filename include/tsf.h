@@ -404,12 +404,13 @@ tsf_status tsf_walk(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_walk_bat
  * header gets done = -4 and reserved = (t << 8) | the failed bits, and its
  * state is written back as it was at that point (not at all when the
  * loaded state failed).  Walks that pass every check end bit-identical to
- * tsf_walk with the same arguments.  Kernels exist for one launch shape per
- * strategy (strategy 0: 3 up to capacity 64, 1 up to capacity 128 when
- * max_len <= 32, else 2; 8 lanes per walk for the attempt-parallel
- * strategies, 64 for the term-parallel one, one wavefront per workgroup);
- * `launch` may be NULL or name one of them, else TSF_E_ARG.  Slower than tsf_walk (the index check is quadratic in the
- * rank).  Errors as tsf_walk. */
+ * tsf_walk with the same arguments.  With `launch` NULL, or its strategy and
+ * lanes_per_walk zero, the shape is the one that tsf_walk chooses for the
+ * batch without a tuned launch, so that the kernel checked is the one that
+ * runs; a launch that names one of them may name 8 lanes per walk for the
+ * attempt-parallel strategies and 64 for the term-parallel one, else TSF_E_ARG
+ * (a zero field as in tsf_walk).  Slower than tsf_walk (the index check is
+ * quadratic in the rank).  Errors as tsf_walk. */
 #define TSF_CHECK_RANK 1u
 #define TSF_CHECK_ZERO_FACTOR 2u
 #define TSF_CHECK_CODING 4u

@@ -2,6 +2,7 @@
 // open, and what the autotuner tries and remembers (host code, no HIP).
 #pragma once
 #include "../../include/tsf.h"
+#include "tsf_internal.h"
 
 #include <stddef.h>
 #include <vector>
@@ -79,6 +80,51 @@ inline tsf_launch default_launch(const tsf_walk_params *prm, const tsf_walk_batc
     const bool sixteen = (ix ? wide || cap > 48 : rank || (cap % 16 == 0 && n <= 16384)) &&
                          launch_rounds(n, 16, lds) <= launch_rounds(n, 8, lds);
     return tsf_launch{sixteen ? 16 : 8, 0, ix ? 3 : 1};
+}
+
+// The shape of a walk call: what its launch names, and the library's choice where it
+// leaves the strategy and the lanes open.  With only one of them named: the indexed
+// strategy up to 64 terms, the attempt-parallel one up to 128 terms of 32-bit
+// factors, the term-parallel one beyond; 8 lanes, 64 of the term-parallel one.
+// Checked calls take the shape that an unchecked one takes, or one of the shapes
+// whose lanes follow from the strategy: other kernels are not built with the checks.
+struct WalkShape {
+    int strategy, lanes, waves;
+};
+inline tsf_status walk_shape(const tsf_walk_params *prm, const tsf_walk_batch *b,
+                             const tsf_launch *launch, bool checked, WalkShape &w)
+{
+    int strategy = launch ? launch->strategy : 0, lanes = launch ? launch->lanes_per_walk : 0;
+    const int waves = launch && launch->waves_per_block ? launch->waves_per_block : 1;
+    if (strategy < 0 || strategy > 3)
+        return tsf_fail(TSF_E_ARG, "strategy %d not in 0..3", strategy);
+    const bool open = strategy == 0 && lanes == 0;
+    if (open) {
+        const tsf_launch d = default_launch(prm, b);
+        strategy = d.strategy;
+        lanes = d.lanes_per_walk;
+    }
+    if (strategy == 0)
+        strategy = b->capacity <= 64 ? 3 : b->capacity <= 128 && b->max_len <= 32 ? 1 : 2;
+    const bool ap = strategy != 2;
+    if (strategy == 3 && b->capacity > 64)
+        return tsf_fail(TSF_E_CAPACITY, "the indexed strategy needs capacity <= 64");
+    if (ap && b->capacity > 128)
+        return tsf_fail(TSF_E_CAPACITY, "the attempt-parallel strategy needs capacity <= 128");
+    if (lanes == 0) lanes = ap ? 8 : 64;
+    if (lanes != 4 && lanes != 8 && lanes != 16 && lanes != 32 && lanes != 64)
+        return tsf_fail(TSF_E_ARG, "lanes_per_walk %d not in {4,8,16,32,64}", lanes);
+    if (lanes == 4 && !ap)
+        return tsf_fail(TSF_E_ARG, "4 lanes per walk only with the attempt-parallel strategies");
+    if (ap && lanes == 64)
+        return tsf_fail(TSF_E_ARG, "the attempt-parallel strategies use 4 to 32 lanes per walk");
+    if (waves < 1 || waves > 4)
+        return tsf_fail(TSF_E_ARG, "waves_per_block %d not in 1..4", waves);
+    if (checked && !open && lanes != (ap ? 8 : 64))
+        return tsf_fail(TSF_E_ARG, "checked walks use %d lanes per walk with this strategy",
+                        ap ? 8 : 64);
+    w = WalkShape{strategy, lanes, waves};
+    return TSF_OK;
 }
 
 // What tsf_autotune times: 4 to 16 lanes of the attempt-parallel strategies, 16 to

@@ -954,33 +954,10 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
     if (prm->objective != TSF_OBJ_RANK && prm->objective != TSF_OBJ_ADDITIONS)
         return tsf_fail(TSF_E_ARG, "objective %d", prm->objective);
     if (b->log && b->log_cap < 0) return tsf_fail(TSF_E_ARG, "log_cap < 0");
-    int strategy = launch ? launch->strategy : 0;
-    if (strategy < 0 || strategy > 3) return tsf_fail(TSF_E_ARG, "strategy %d not in 0..3", strategy);
-    const bool wide = b->max_len > 32;
-    int g = launch ? launch->lanes_per_walk : 0;
-    if (strategy == 0 && g == 0 && !checked) {
-        const tsf_launch d = default_launch(prm, b);
-        strategy = d.strategy;
-        g = d.lanes_per_walk;
-    }
-    // lanes without a strategy, and the checked kernels: the indexed strategy up
-    // to 64 terms, the attempt-parallel one up to 128 terms of 32-bit factors
-    if (strategy == 0) strategy = b->capacity <= 64 ? 3 : (b->capacity <= 128 && !wide ? 1 : 2);
-    const bool ap = strategy == 1 || strategy == 3;
-    const bool ix = strategy == 3;
-    if (ix && b->capacity > 64)
-        return tsf_fail(TSF_E_CAPACITY, "the indexed strategy needs capacity <= 64");
-    if (ap && b->capacity > 128)
-        return tsf_fail(TSF_E_CAPACITY, "the attempt-parallel strategy needs capacity <= 128");
-    if (g == 0) g = ap ? 8 : 64;
-    int wpb = launch && launch->waves_per_block ? launch->waves_per_block : 1;
-    if (g != 4 && g != 8 && g != 16 && g != 32 && g != 64)
-        return tsf_fail(TSF_E_ARG, "lanes_per_walk %d not in {4,8,16,32,64}", g);
-    if (g == 4 && !ap)
-        return tsf_fail(TSF_E_ARG, "4 lanes per walk only with the attempt-parallel strategies");
-    if (ap && g == 64)
-        return tsf_fail(TSF_E_ARG, "the attempt-parallel strategies use 4 to 32 lanes per walk");
-    if (wpb < 1 || wpb > 4) return tsf_fail(TSF_E_ARG, "waves_per_block %d not in 1..4", wpb);
+    WalkShape w;
+    if ((st = walk_shape(prm, b, launch, checked, w))) return st;
+    const bool wide = b->max_len > 32, ix = w.strategy == 3, ap = ix || w.strategy == 1;
+    const int g = w.lanes, wpb = w.waves;
     // term slots per lane (term-parallel kernels), or 64-bit words of a
     // partner set (attempt-parallel kernels)
     const int s = ap ? (b->capacity > 64 ? 2 : 1) : slots_for(b->capacity, g);
@@ -990,10 +967,7 @@ tsf_status prepare_walk(const tsf_walk_params *prm, const tsf_walk_batch *b, int
     // factors of at most 16 entries: the indexed kernels keep each factor's
     // digits and signs in one 32-bit LDS word
     const bool pk = ix && !wide && b->max_len <= 16;
-    if (checked && g != (ap ? 8 : 64))
-        return tsf_fail(TSF_E_ARG, "checked walks use %d lanes per walk with this strategy",
-                        ap ? 8 : 64);
-    L.fn = pick_kernel(g, s, wide, b->mode == TSF_Z2, learned ? 5 : pk ? 4 : strategy, checked);
+    L.fn = pick_kernel(g, s, wide, b->mode == TSF_Z2, learned ? 5 : pk ? 4 : w.strategy, checked);
     if (!L.fn) return tsf_fail(TSF_E_ARG, "no kernel for this configuration");
     const int walks_per_wave = 64 / g;
     const int cap2 = lds_stride(b->capacity, ix);

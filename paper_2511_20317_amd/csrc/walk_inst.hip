@@ -16,13 +16,13 @@ namespace tsfk {
 using Word = std::conditional_t<TSFK_WIDE != 0, uint64_t, uint32_t>;
 constexpr bool kZ2 = TSFK_Z2 != 0;
 
-// a walk kernel, or its checked variant (tsf_walk_checked), which exists for
-// the default launch shapes only: 8 lanes per walk for the attempt-parallel
-// strategies, 64 for the term-parallel one
+// a walk kernel, or its checked variant (tsf_walk_checked), which exists for the
+// shapes that the library chooses by itself and for 8 lanes per walk of the
+// attempt-parallel strategies
 template <int G, int S, bool AP, bool IX, bool PK = false>
 KernelFn kern(bool chk)
 {
-    if constexpr ((G == 8 && AP) || (G == 64 && !AP)) {
+    if constexpr (AP ? G == 8 || (IX ? G >= 16 : G == 16 && S == 2) : G == 64) {
         if (chk) return walk_kernel_checked<G, S, Word, kZ2, AP, IX, PK>;
     }
     if (chk) return nullptr;

@@ -3,6 +3,8 @@
 
 #include <cstring>
 
+tsf_status tsf_fail(tsf_status st, const char *, ...) { return st; }
+
 static void batch(int cap, int max_len, int n, int objective, tsf_walk_params &prm,
                   tsf_walk_batch &b)
 {
@@ -49,4 +51,17 @@ extern "C" int shim_serves(const int *tuned, const int *other)
     a.mode = tuned[4];
     b.mode = other[4];
     return tune_serves(tune_entry(&p, &a, tsf_launch{8, 1, 1}), &q, &b);
+}
+
+// the shape of a call: 1000 * strategy + 10 * lanes + wavefronts, or its status
+extern "C" int shim_shape(int cap, int max_len, int n, int objective, int strategy, int lanes,
+                          int waves, int checked)
+{
+    tsf_walk_params prm;
+    tsf_walk_batch b;
+    batch(cap, max_len, n, objective, prm, b);
+    const tsf_launch l{lanes, waves, strategy};
+    WalkShape w;
+    const tsf_status st = walk_shape(&prm, &b, &l, checked != 0, w);
+    return st ? st : 1000 * w.strategy + 10 * w.lanes + w.waves;
 }

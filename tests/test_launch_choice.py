@@ -63,3 +63,28 @@ def test_tuned_launch_serves_its_kind_of_batch_alone(shim):
     assert serves(tuned, tuned) and serves(tuned, [88, 20, 17000, 0, 0])
     for k, other in enumerate((87, 16, 32768, 1, 1)):
         assert not serves(tuned, tuned[:k] + [other] + tuned[k + 1:])
+
+
+def test_checked_walks_take_the_shape_of_unchecked_ones(shim):
+    shapes = set()
+    for cap in (12, 35, 41, 49, 64, 65, 72, 88, 96, 97, 128, 129, 512):
+        for walks in (1, 1024, 3073, 4097, 8193, 18432, 65536):
+            for max_len in (9, 32, 64):
+                for objective in (0, 1):
+                    for waves in (0, 4):
+                        call = (cap, max_len, walks, objective, 0, 0, waves)
+                        shapes.add(shim.shim_shape(*call, 0))
+                        assert shim.shim_shape(*call, 1) == shim.shim_shape(*call, 0) > 0
+                    # named: one shape a strategy, or refused
+                    for strategy in (0, 1, 2, 3):
+                        for lanes in (0, 4, 8, 16, 32, 64):
+                            if strategy == lanes == 0:
+                                continue
+                            plain = shim.shim_shape(cap, max_len, walks, objective, strategy,
+                                                    lanes, 1, 0)
+                            check = shim.shim_shape(cap, max_len, walks, objective, strategy,
+                                                    lanes, 1, 1)
+                            one = plain > 0 and plain // 10 % 100 == (64 if plain // 1000 == 2
+                                                                      else 8)
+                            assert check == (plain if one or plain < 0 else -1)
+    assert {s // 10 for s in shapes} >= {264, 332, 316, 308, 116, 108}
