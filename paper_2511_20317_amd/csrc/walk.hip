@@ -352,18 +352,22 @@ __global__ void __launch_bounds__(64) meta_kernel(tsf_walk_batch in, int32_t whi
 // Feature rows of the proposal network from log records: a wavefront writes a
 // row of 1 KiB with one 16-byte store per lane.  A record is 128 bytes, so the
 // kernel is bound by its writes; one row per thread, whose stores went to 64
-// different rows at a time, took 14 us for 4,096 rows.
+// different rows at a time, took 14 us for 4,096 rows.  A launch has at most
+// 65,536 workgroups, which take further rows in turn: with a workgroup for every
+// four rows, launches would end at 2^32 threads, 64 GiB of features.
+constexpr int64_t kFeatureBlocks = 65536;
 __global__ void __launch_bounds__(256) features_kernel(const tsf_flip_log *log, int64_t n,
                                                        uint16_t *X)
 {
-    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (q >= n) return;
-    const tsf_flip_log &lg = log[q];
     const int lane = threadIdx.x & 63;
     const int b = lane < 48 ? lane >> 3 : 0;
-    const int slot = lg.format_slot < 0 || lg.format_slot > 15 ? 15 : lg.format_slot;
-    store_feature_piece(X + q * 512, lane,
-                        feature_piece(lane, lg.f[2 * b], lg.f[2 * b + 1], slot, lg.rank_before));
+    for (int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); q < n;
+         q += (int64_t)gridDim.x * 4) {
+        const tsf_flip_log &lg = log[q];
+        const int slot = lg.format_slot < 0 || lg.format_slot > 15 ? 15 : lg.format_slot;
+        store_feature_piece(X + q * 512, lane,
+                            feature_piece(lane, lg.f[2 * b], lg.f[2 * b + 1], slot, lg.rank_before));
+    }
 }
 
 // Isotropy invariants (Sec. 3.7) of one scheme per wavefront: lane l takes
@@ -1283,7 +1287,9 @@ tsf_status tsf_features_from_log(const tsf_flip_log *log, int64_t n, uint16_t *X
 {
     if (n < 0 || (n > 0 && (!log || !X))) return tsf_fail(TSF_E_ARG, "bad feature arguments");
     if (n == 0) return TSF_OK;
-    hipLaunchKernelGGL(features_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0,
+    const int64_t blocks = n / 4 + (n % 4 != 0);
+    hipLaunchKernelGGL(features_kernel,
+                       dim3((unsigned)(blocks < kFeatureBlocks ? blocks : kFeatureBlocks)), dim3(256), 0,
                        (hipStream_t)hip_stream, log, n, X);
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "feature launch failed");
     return TSF_OK;
