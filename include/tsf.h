@@ -628,8 +628,9 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
  * search runs.  Everything else in the iteration is unchanged, so every scheme
  * is exact and verified as before.  The attempts counter grows by K per
  * iteration.  Workspace (device, caller-owned), R = 8 * n_walks rows:
- * cand R uint32, feat R x 512 bf16, h1 and h2 R x 256 bf16 (required, contents
- * undefined), logit R fp32.
+ * cand R uint32, feat R x 512 bf16, h1 and h2 R x 256 bf16, logit R fp32; after
+ * the call they hold the last iteration's candidates, their rows, the hidden
+ * layers and the scores.
  * choice (optional, device): choice_cap bytes per walk; the attempt applied at
  * iteration t (255 = fallback) goes to w*choice_cap + t-1 while t <= choice_cap.
  * Runs n_iters iterations (each the network and a kernel that applies the

@@ -1201,9 +1201,12 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
     };
     // score the proposed candidates, then apply the best and, but in the call's
     // last iteration, propose the next ones: the scheme is loaded once an
-    // iteration.  The hidden layers stay in the network's kernel.
+    // iteration.  The hidden layers stay in the network's kernel, but for those
+    // of the last iteration, which the caller finds beside its rows and scores.
     auto iteration = [&](hipStream_t on, bool last) -> tsf_status {
-        const tsf_status e = mlp_forward(net, ws->feat, (int32_t)rows, nullptr, nullptr, ws->logit, on);
+        const tsf_status e =
+            mlp_forward(net, ws->feat, (int32_t)rows, last ? ws->h1 : nullptr,
+                        last ? ws->h2 : nullptr, ws->logit, on);
         return e ? e : walks(last ? 2 : 3, on);
     };
     if ((st = walks(1, s))) return st;
@@ -1220,7 +1223,7 @@ tsf_status tsf_walk_learned(tsf_ctx *ctx, const tsf_walk_params *prm, const tsf_
     std::memset(key, 0, sizeof key);
     a.phase = 0;
     std::memcpy(key, &a, sizeof a);
-    const void *ptrs[8] = {net->param, net->wbf, ws->cand, ws->feat, ws->h1, ws->h2, ws->logit,
+    const void *ptrs[8] = {net->param, net->wbf, ws->cand, ws->feat, ws->logit,
                            (const void *)L.fn};
     std::memcpy(key + sizeof a, ptrs, sizeof ptrs);
     GraphEntry *ge = nullptr;
