@@ -38,9 +38,17 @@ constexpr int kLiftMaxEq = 8192;     // equations (mn)(np)(pm) searched on the G
 constexpr int kLiftMaxTerms = 512;
 
 // What a search leaves: the smallest subtree with a solution, the smallest that
-// ran out of budget, the number searched to the end.
+// ran out of budget, the numbers searched to the end.  Atomics on one address
+// wait for each other, so the subtrees count in kCounters lines of memory in
+// turn, and only a subtree below them writes the two minima: a search of a
+// (2,2,2) scheme with 65,536 subtrees of at most 16 nodes takes 83 us, 1,262 us
+// with one counter and every subtree's minimum written.
+constexpr int kCounters = 64;
 struct LiftOut {
-    unsigned long long first, budget, exhausted;
+    unsigned long long first, budget;
+    struct {
+        unsigned long long n, pad[15];
+    } exhausted[kCounters];
 };
 
 struct LiftArgs {
@@ -193,9 +201,14 @@ __global__ void __launch_bounds__(64) lift_kernel(LiftArgs a)
         return;
     }
     if (lane == 0) {
-        if (status == 1) atomicMin(&a.out->first, (unsigned long long)sub);
-        if (status == 2) atomicMin(&a.out->budget, (unsigned long long)sub);
-        if (status <= 1) atomicAdd(&a.out->exhausted, 1ull);
+        // (a minimum read late only looks larger than it is)
+        const auto lower = [&](unsigned long long *to) {
+            if (__atomic_load_n(to, __ATOMIC_RELAXED) > (unsigned long long)sub)
+                atomicMin(to, (unsigned long long)sub);
+        };
+        if (status == 1) lower(&a.out->first);
+        if (status == 2) lower(&a.out->budget);
+        if (status <= 1) atomicAdd(&a.out->exhausted[sub % kCounters].n, 1ull);
     }
 }
 
@@ -271,7 +284,7 @@ tsf_status tsf_lift(const tsf_scheme *z2, int64_t max_nodes, int32_t max_subtree
                  o_free = o_off + (size_t)(r + 1) * 4, o_eq = o_free + (size_t)r * 4,
                  o_rem = o_eq + np * 2, bytes = o_rem + (size_t)E * 2;
     std::vector<unsigned char> blob(bytes);
-    const LiftOut none{~0ull, ~0ull, 0};
+    const LiftOut none{~0ull, ~0ull, {}};
     std::memcpy(blob.data(), &none, sizeof none);
     std::memset(blob.data() + o_pat, 0, (size_t)r * 8);
     std::memcpy(blob.data() + o_mask, mask.data(), np * 8);
@@ -306,7 +319,7 @@ tsf_status tsf_lift(const tsf_scheme *z2, int64_t max_nodes, int32_t max_subtree
         std::memset(res, 0, sizeof *res);
         res->subtrees = n_sub;
         res->prefix_terms = P;
-        res->exhausted = (int64_t)got.exhausted;
+        for (const auto &c : got.exhausted) res->exhausted += (int64_t)c.n;
         if (got.first != ~0ull) {
             res->status = got.first < got.budget ? 1 : 2;
             res->subtree = (int64_t)got.first;
