@@ -605,15 +605,17 @@ tsf_status tsf_mlp_sync(const tsf_mlp *net, void *hip_stream);
 
 /* Forward pass of M rows: X (device, M x 512 bf16, row-major) -> h1, h2
  * (device, M x 256 bf16 each, caller workspace) and logit (device, M fp32).
- * Async on the stream.  Errors: TSF_E_ARG, TSF_E_DEVICE. */
+ * h2 and logit may lie over X, and logit over h1; such calls take the pass in
+ * steps and are slower.  Async on the stream.  Errors: TSF_E_ARG, TSF_E_DEVICE. */
 tsf_status tsf_mlp_fwd(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_t *h1,
                        uint16_t *h2, float *logit, void *hip_stream);
 
 /* Backward pass of the mean binary cross-entropy against labels y (device, M
  * fp32 in {0,1}), using the forward's h1, h2, logit: writes every gradient into
  * net->grad (overwriting it) and the loss into *loss (device fp32).  d2, d1
- * (device, M x 256 bf16) and d3 (device, M fp32) are caller workspace.
- * Async on the stream.  Errors: TSF_E_ARG, TSF_E_DEVICE. */
+ * (device, M x 256 bf16) and d3 (device, M fp32) are caller workspace.  d1 may be
+ * h1 or lie over h2, and d3 may be logit; such calls take the pass in steps and
+ * are slower.  Async on the stream.  Errors: TSF_E_ARG, TSF_E_DEVICE. */
 tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, int32_t M,
                        const uint16_t *h1, const uint16_t *h2, const float *logit, uint16_t *d2,
                        uint16_t *d1, float *d3, float *loss, void *hip_stream);

@@ -236,6 +236,19 @@ __device__ __forceinline__ void tile_out(const Block<RB, WR> &B, uint16_t *out, 
     }
 }
 
+// rows of global memory into the tile, zeros past the end
+template <int RB, int WR, bool AL>
+__device__ __forceinline__ void tile_in(const Block<RB, WR> &B, const uint16_t *in, int row0, int M)
+{
+#pragma unroll
+    for (int t = 0; t < 4 * RB; ++t) {
+        const int r = (threadIdx.x >> 5) + 8 * WR * t, c = (threadIdx.x & 31) * 8;
+        v4u32 v = {0, 0, 0, 0};
+        if (row0 + r < M) v = load8<AL>(in + (int64_t)(row0 + r) * HID + c);
+        *reinterpret_cast<v4u32 *>(B.tile + r * LDT + c) = v;
+    }
+}
+
 // Sums over the wavefront's lanes, in the order of a butterfly over lane
 // distances 32, 16, 8, 4, 2, 1.  The first two steps of four sums share their
 // instructions: a swap of the halves (quarters) of two registers leaves one
@@ -283,6 +296,7 @@ struct FwdArgs {
     int M;
     uint16_t *h1, *h2;  // null: not stored
     float *logit;
+    int step;           // of a pass in steps
 };
 
 // The forward pass of a block of rows.  Layer 1 reads X (1 KiB a row) and W1
@@ -292,7 +306,10 @@ struct FwdArgs {
 // it products and LDS traffic alone); as a GEMM per layer and a kernel for the
 // logit they took 38.8 us.  At 4,096 rows the weights through each workgroup
 // bound it: 10.1 us, of which 3.7 us are their reads.
-template <int RB, int WR, bool AL>
+// STEPS: one step of the pass, from the buffers of the one before: 0 the first
+// layer, 1 the second, 2 the logit.  For calls whose h2 or logit lies over an
+// input of an earlier step; a block would overwrite rows that others still read.
+template <int RB, int WR, bool AL, bool STEPS = false>
 __global__ void __launch_bounds__(256 * WR) fwd_kernel(FwdArgs g)
 {
     using Bl = Block<RB, WR>;
@@ -301,54 +318,67 @@ __global__ void __launch_bounds__(256 * WR) fwd_kernel(FwdArgs g)
     B.W = smem;
     B.tile = smem + 2 * kWBuf;
     const int row0 = blockIdx.x * Bl::R;
-    // this thread's pieces of an X chunk (rows past the end read the last one)
-    const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 8;
-    const uint16_t *xsrc[RB];
+    if (!STEPS || g.step == 0) {
+        // this thread's pieces of an X chunk (rows past the end read the last one)
+        const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 8;
+        const uint16_t *xsrc[RB];
 #pragma unroll
-    for (int t = 0; t < RB; ++t) {
-        const int r = row0 + xr + 32 * WR * t;
-        xsrc[t] = g.X + (int64_t)(r < g.M ? r : g.M - 1) * IN + xc;
-    }
-    const auto load_x = [&](int c, int q) {
-#pragma unroll
-        for (int t = 0; t < RB; ++t) B.xreg[q][t] = load8<AL>(xsrc[t] + c * BK);
-    };
-    constexpr int C1 = IN / BK;
-#pragma unroll
-    for (int c = 0; c < kAhead; ++c) {
-        B.template load_w<AL>(g.w1t + c * BK, IN, c);
-        load_x(c, c);
-    }
-    B.clear();
-#pragma unroll 1
-    for (int c0 = 0; c0 < C1; c0 += kAhead) {
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) {
-            const int c = c0 + q;
-            uint16_t *xb = B.tile + q * Bl::kXBuf;
-            B.store_w(q, q);
-#pragma unroll
-            for (int t = 0; t < RB; ++t)
-                *reinterpret_cast<v4u32 *>(xb + (xr + 32 * WR * t) * LDK + xc) = B.xreg[q][t];
-            // the chunk two steps on, of W1 or the first ones of W2
-            const int cn = c + kAhead;
-            const bool more = cn < C1;
-            B.template load_w<AL>(more ? g.w1t + cn * BK : g.w2t + (cn - C1) * BK,
-                                  more ? IN : HID, q);
-            if (more) load_x(cn, q);
-            __syncthreads();
-            B.multiply(q, xb, LDK);
+        for (int t = 0; t < RB; ++t) {
+            const int r = row0 + xr + 32 * WR * t;
+            xsrc[t] = g.X + (int64_t)(r < g.M ? r : g.M - 1) * IN + xc;
         }
+        const auto load_x = [&](int c, int q) {
+#pragma unroll
+            for (int t = 0; t < RB; ++t) B.xreg[q][t] = load8<AL>(xsrc[t] + c * BK);
+        };
+        constexpr int C1 = IN / BK;
+#pragma unroll
+        for (int c = 0; c < kAhead; ++c) {
+            B.template load_w<AL>(g.w1t + c * BK, IN, c);
+            load_x(c, c);
+        }
+        B.clear();
+#pragma unroll 1
+        for (int c0 = 0; c0 < C1; c0 += kAhead) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int c = c0 + q;
+                uint16_t *xb = B.tile + q * Bl::kXBuf;
+                B.store_w(q, q);
+#pragma unroll
+                for (int t = 0; t < RB; ++t)
+                    *reinterpret_cast<v4u32 *>(xb + (xr + 32 * WR * t) * LDK + xc) = B.xreg[q][t];
+                // the chunk two steps on, of W1 or the first ones of W2
+                const int cn = c + kAhead;
+                const bool more = cn < C1;
+                B.template load_w<AL>(more ? g.w1t + cn * BK : g.w2t + (cn - C1) * BK,
+                                      more ? IN : HID, q);
+                if (more) load_x(cn, q);
+                __syncthreads();
+                B.multiply(q, xb, LDK);
+            }
+        }
+        __syncthreads();
+        relu_to_tile<RB, WR>(B, g.b1);
+        __syncthreads();
+        if (g.h1) tile_out<RB, WR, AL>(B, g.h1, row0, g.M);
     }
-    __syncthreads();
-    relu_to_tile<RB, WR>(B, g.b1);
-    __syncthreads();
-    if (g.h1) tile_out<RB, WR, AL>(B, g.h1, row0, g.M);
-    B.clear();
-    B.template layer_on_tile<AL>(g.w2t);
-    relu_to_tile<RB, WR>(B, g.b2);
-    __syncthreads();
-    if (g.h2) tile_out<RB, WR, AL>(B, g.h2, row0, g.M);
+    if constexpr (STEPS) {
+        if (g.step == 0) return;
+        tile_in<RB, WR, AL>(B, g.step == 1 ? g.h1 : g.h2, row0, g.M);
+        if (g.step == 1)
+#pragma unroll
+            for (int c = 0; c < kAhead; ++c) B.template load_w<AL>(g.w2t + c * BK, HID, c);
+    }
+    if (!STEPS || g.step == 1) {
+        B.clear();
+        B.template layer_on_tile<AL>(g.w2t);
+        relu_to_tile<RB, WR>(B, g.b2);
+        __syncthreads();
+        if (g.h2) tile_out<RB, WR, AL>(B, g.h2, row0, g.M);
+        if constexpr (STEPS) return;
+    }
+    if constexpr (STEPS) __syncthreads();
     // logit: lane l sums columns l, l+64, l+128, l+192 of a row
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float w3[4];
@@ -385,12 +415,14 @@ struct DeltaArgs {
     int M;
     float *d3;
     uint16_t *d2, *d1;
+    int step;           // of a pass in steps
 };
 
 // delta3 = (sigmoid(logit) - y) / M; delta2 = bf16(delta3 w3 [h2 > 0]);
-// delta1 = bf16((delta2 W2^T) [h1 > 0]) for 32*RB rows; delta2 stays in LDS as
+// delta1 = bf16((delta2 W2^T) [h1 > 0]) for 32*RB*WR rows; delta2 stays in LDS as
 // the operand of its product.
-template <int RB, int WR, bool AL>
+// STEPS: one step of the pass: 0 delta3 and delta2, 1 delta1 from them.
+template <int RB, int WR, bool AL, bool STEPS = false>
 __global__ void __launch_bounds__(256 * WR) delta_kernel(DeltaArgs g)
 {
     using Bl = Block<RB, WR>;
@@ -402,36 +434,41 @@ __global__ void __launch_bounds__(256 * WR) delta_kernel(DeltaArgs g)
     const int row0 = blockIdx.x * Bl::R;
 #pragma unroll
     for (int c = 0; c < kAhead; ++c) B.template load_w<AL>(g.w2 + c * BK, HID, c);
-    if (threadIdx.x < Bl::R) {
-        const int r = row0 + threadIdx.x;
-        float d = 0.0f;
-        if (r < g.M) {
-            d = logit_delta(g.logit[r], g.y[r], g.M);
-            g.d3[r] = d;
-        }
-        dz[threadIdx.x] = d;
-    }
     const int c8 = (threadIdx.x & 31) * 8;
-    float w3[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) w3[q] = from_bf16(g.w3[c8 + q]);
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 4 * RB; ++t) {
-        const int r = (threadIdx.x >> 5) + 8 * WR * t;
-        v4u32 o = {0, 0, 0, 0};
-        if (row0 + r < g.M) {
-            const v4u32 h = load8<AL>(g.h2 + (int64_t)(row0 + r) * HID + c8);
-            const float d = dz[r];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float lo = from_bf16((uint16_t)h[q]), hi = from_bf16((uint16_t)(h[q] >> 16));
-                o[q] = pack_bf16(lo > 0.0f ? d * w3[2 * q] : 0.0f, hi > 0.0f ? d * w3[2 * q + 1] : 0.0f);
+    if (!STEPS || g.step == 0) {
+        if (threadIdx.x < Bl::R) {
+            const int r = row0 + threadIdx.x;
+            float d = 0.0f;
+            if (r < g.M) {
+                d = logit_delta(g.logit[r], g.y[r], g.M);
+                g.d3[r] = d;
             }
-            store8<AL>(g.d2 + (int64_t)(row0 + r) * HID + c8, o);
+            dz[threadIdx.x] = d;
         }
-        *reinterpret_cast<v4u32 *>(B.tile + r * LDT + c8) = o;
+        float w3[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w3[q] = from_bf16(g.w3[c8 + q]);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 4 * RB; ++t) {
+            const int r = (threadIdx.x >> 5) + 8 * WR * t;
+            v4u32 o = {0, 0, 0, 0};
+            if (row0 + r < g.M) {
+                const v4u32 h = load8<AL>(g.h2 + (int64_t)(row0 + r) * HID + c8);
+                const float d = dz[r];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float lo = from_bf16((uint16_t)h[q]), hi = from_bf16((uint16_t)(h[q] >> 16));
+                    o[q] = pack_bf16(lo > 0.0f ? d * w3[2 * q] : 0.0f, hi > 0.0f ? d * w3[2 * q + 1] : 0.0f);
+                }
+                store8<AL>(g.d2 + (int64_t)(row0 + r) * HID + c8, o);
+            }
+            *reinterpret_cast<v4u32 *>(B.tile + r * LDT + c8) = o;
+        }
+    } else {
+        tile_in<RB, WR, AL>(B, g.d2, row0, g.M);
     }
+    if (STEPS && g.step == 0) return;
     B.clear();
     // delta1[m][k] = sum_n delta2[m][n] W2[k][n]
     B.template layer_on_tile<AL>(g.w2);
@@ -454,9 +491,10 @@ __global__ void __launch_bounds__(256 * WR) delta_kernel(DeltaArgs g)
 
 struct GradArgs {
     const uint16_t *X, *h1, *h2, *d1, *d2;
-    const float *d3, *logit, *y;
+    const float *d3, *logit, *y;  // d3 null: taken from the logits (db3, loss)
     int M;
     float *grad, *loss;
+    int first;                    // the launch's first block
 };
 
 constexpr int kGradWaves = 16;
@@ -495,13 +533,13 @@ __global__ void __launch_bounds__(1024) grad_kernel(GradArgs g)
     __shared__ __attribute__((aligned(16))) uint16_t stage[kGradWaves][2][32 * 32];
     __shared__ float sums[kGradWaves][32];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int block = g.first + (int)blockIdx.x, x = block & 7, j = block >> 3;
     if (j == 25) {
         // db3 and the loss
         float sd = 0.0f, sl = 0.0f;
         for (int m = threadIdx.x; m < g.M; m += 64 * kGradWaves) {
-            sd += g.d3[m];
             const float z = g.logit[m];
+            sd += g.d3 ? g.d3[m] : logit_delta(z, g.y[m], g.M);
             // softplus(z) - y z, computed stably
             const float sp = z > 0.0f ? z + log1pf(__expf(-z)) : log1pf(__expf(z));
             sl += (sp - g.y[m] * z) / (float)g.M;
@@ -619,7 +657,8 @@ __global__ void __launch_bounds__(1024) grad_kernel(GradArgs g)
         g.grad[(first ? O_B1 : O_B2) + n0 + threadIdx.x] = t;
     }
 }
-constexpr int kGradBlocks = 8 * 25 + 1;
+// blocks: dW1 and db1, dW2 and db2, dW3, then one for db3 and the loss
+constexpr int kGradW1 = 0, kGradW2 = 8 * 16, kGradB3 = 8 * 25, kGradBlocks = kGradB3 + 1;
 // `stage` holds a wavefront's operands and later its partial tile
 static_assert(2 * 32 * 32 * sizeof(uint16_t) == 32 * 32 * sizeof(float), "stage size");
 
@@ -663,6 +702,13 @@ __global__ void __launch_bounds__(256) sync_kernel(const float *p, uint16_t *q)
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// whether two arrays of M rows of `a` and `b` bytes share memory
+bool overlap(const void *p, int64_t a, const void *q, int64_t b, int64_t M)
+{
+    const char *x = (const char *)p, *y = (const char *)q;
+    return p && q && x < y + M * b && y < x + M * a;
+}
+
 // The rows of a workgroup, by what fills the 256 CUs in one turn: 128 rows
 // (eight wavefronts) above 16,384 rows, 64 above 8,192, 32 below.  The weights,
 // 384 KiB through every workgroup, favour large blocks (32,768 rows: 19.9 us
@@ -688,9 +734,18 @@ tsf_status mlp_forward(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_
     if (st) return st;
     if (M == 0) return TSF_OK;
     if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
-    const FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
-                    net->param + O_B2, net->param + O_B3, M, h1, h2, logit};
+    FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
+              net->param + O_B2, net->param + O_B3, M, h1, h2, logit, 0};
     const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2);
+    constexpr int kX = 2 * IN, kH = 2 * HID;
+    if (h1 && h2 && (overlap(h2, kH, X, kX, M) || overlap(logit, 4, X, kX, M) ||
+                     overlap(logit, 4, h1, kH, M))) {
+        auto *fn = al ? fwd_kernel<1, 1, true, true> : fwd_kernel<1, 1, false, true>;
+        for (g.step = 0; g.step < 3; ++g.step)
+            hipLaunchKernelGGL(fn, dim3((M + 31) / 32), dim3(256), 0, (hipStream_t)hip_stream, g);
+        if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "forward launch failed");
+        return TSF_OK;
+    }
     const int rows = al ? rows_per_block(M) : 32;
     auto *fn = !al ? fwd_kernel<1, 1, false> : rows == 128 ? fwd_kernel<2, 2, true>
                                              : rows == 64 ? fwd_kernel<1, 2, true>
@@ -736,14 +791,36 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
     const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2) &&
                     aligned16(d1) && aligned16(d2);
     const int rows = al ? rows_per_block(M) : 32;
-    const DeltaArgs d{logit, y, h1, h2, net->wbf + Q_W2, net->wbf + Q_W3, M, d3, d2, d1};
-    auto *dfn = !al ? delta_kernel<1, 1, false> : rows == 128 ? delta_kernel<2, 2, true>
-                                                : rows == 64 ? delta_kernel<1, 2, true>
-                                                             : delta_kernel<1, 1, true>;
-    hipLaunchKernelGGL(dfn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0, s, d);
-    const GradArgs g{X, h1, h2, d1, d2, d3, logit, y, M, net->grad, loss};
+    DeltaArgs d{logit, y, h1, h2, net->wbf + Q_W2, net->wbf + Q_W3, M, d3, d2, d1, 0};
+    GradArgs g{X, h1, h2, d1, d2, d3, logit, y, M, net->grad, loss, 0};
     auto *gfn = al ? grad_kernel<true> : grad_kernel<false>;
-    hipLaunchKernelGGL(gfn, dim3(kGradBlocks), dim3(64 * kGradWaves), 0, s, g);
+    const auto grads = [&](int from, int to) {
+        g.first = from;
+        hipLaunchKernelGGL(gfn, dim3(to - from), dim3(64 * kGradWaves), 0, s, g);
+    };
+    constexpr int kH = 2 * HID;
+    if (overlap(d3, 4, logit, 4, M) || overlap(d1, kH, h1, kH, M) || overlap(d1, kH, h2, kH, M) ||
+        overlap(d1, kH, logit, 4, M) || overlap(d1, kH, y, 4, M) || overlap(d1, kH, d3, 4, M)) {
+        // a workspace over an input: every input is used before it is overwritten
+        auto *dfn = al ? delta_kernel<1, 1, true, true> : delta_kernel<1, 1, false, true>;
+        const auto delta = [&](int step) {
+            d.step = step;
+            hipLaunchKernelGGL(dfn, dim3((M + 31) / 32), dim3(256), 0, s, d);
+        };
+        g.d3 = nullptr;
+        grads(kGradB3, kGradBlocks);
+        g.d3 = d3;
+        delta(0);
+        grads(kGradW2, kGradB3);
+        delta(1);
+        grads(kGradW1, kGradW2);
+    } else {
+        auto *dfn = !al ? delta_kernel<1, 1, false> : rows == 128 ? delta_kernel<2, 2, true>
+                                                    : rows == 64 ? delta_kernel<1, 2, true>
+                                                                 : delta_kernel<1, 1, true>;
+        hipLaunchKernelGGL(dfn, dim3((M + rows - 1) / rows), dim3(rows > 32 ? 512 : 256), 0, s, d);
+        grads(0, kGradBlocks);
+    }
     if (hipGetLastError() != hipSuccess) return tsf_fail(TSF_E_DEVICE, "backward launch failed");
     return TSF_OK;
 }
