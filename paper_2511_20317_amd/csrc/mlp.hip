@@ -81,8 +81,9 @@ __device__ __forceinline__ void store8(uint16_t *p, v4u32 v)
 }
 
 // ---------------------------------------------------------------------------
-// A block of 32*RB rows through 256-wide layers: four wavefronts, wavefront w
-// owns the output columns 64w .. 64w+63 of every row of the block.  The weight
+// A block of 32*RB*WR rows through 256-wide layers: WR groups of four wavefronts,
+// 32*RB rows a group; wavefront w of a group owns the output columns
+// 64w .. 64w+63 of each of its rows.  The weight
 // matrices (256 rows of the output column, k contiguous) stream through LDS 64
 // k at a time, double buffered, and kAhead chunks are in flight to registers
 // before that.  The rows' activations come from a 64-wide chunk beside it
@@ -716,7 +717,8 @@ bool overlap(const void *p, int64_t a, const void *q, int64_t b, int64_t M)
 // with 64).
 int rows_per_block(int M) { return M > 16384 ? 128 : M > 8192 ? 64 : 32; }
 
-// the largest M that the row blocks of the forward and backward pass accept
+// The most rows that a pass takes: a launch has at most 2^32 threads, eight per
+// row with 32-row blocks, and rows are numbered in 32 bits; both are far away.
 constexpr int kMaxRows = 65535 * 64;
 
 tsf_status check_net(const tsf_mlp *net)
@@ -733,7 +735,7 @@ tsf_status mlp_forward(const tsf_mlp *net, const uint16_t *X, int32_t M, uint16_
     tsf_status st = check_net(net);
     if (st) return st;
     if (M == 0) return TSF_OK;
-    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
+    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "%d rows exceed the %d of a call", M, kMaxRows);
     FwdArgs g{X, net->wbf + Q_W1T, net->wbf + Q_W2T, net->wbf + Q_W3, net->param + O_B1,
               net->param + O_B2, net->param + O_B3, M, h1, h2, logit, 0};
     const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2);
@@ -786,7 +788,7 @@ tsf_status tsf_mlp_bwd(const tsf_mlp *net, const uint16_t *X, const float *y, in
     if (!net->grad) return tsf_fail(TSF_E_ARG, "null gradient buffer");
     if (M <= 0 || !X || !y || !h1 || !h2 || !logit || !d2 || !d1 || !d3 || !loss)
         return tsf_fail(TSF_E_ARG, "bad backward arguments");
-    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "GEMM with %d rows exceeds the grid", M);
+    if (M > kMaxRows) return tsf_fail(TSF_E_ARG, "%d rows exceed the %d of a call", M, kMaxRows);
     hipStream_t s = (hipStream_t)hip_stream;
     const bool al = aligned16(X) && aligned16(net->wbf) && aligned16(h1) && aligned16(h2) &&
                     aligned16(d1) && aligned16(d2);

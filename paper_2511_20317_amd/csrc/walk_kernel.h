@@ -272,9 +272,8 @@ struct Walker {
     // a fingerprint in a register (see the section FP below)
     static constexpr bool kFP = !AP && G == 64;
     uint32_t fp[kFP ? S : 1][3];
-    static constexpr bool kClose = kFP;
     bool fp_stale;  // the fingerprints do not describe the terms in LDS
-    // kClose: the lane's slots whose terms may agree with another term in two
+    // kFP: the lane's slots whose terms may agree with another term in two
     // fingerprints (both terms of such a pair are in it), and whether this
     // iteration's flip wrote a fingerprint that another term has
     uint32_t close;
@@ -679,7 +678,7 @@ struct Walker {
         if (tr0 == h) tr0 = -1;
         if (tr1 == h) tr1 = -1;
         fp_stale = true;
-        if constexpr (kClose) set_close(h, true);
+        if constexpr (kFP) set_close(h, true);
         if constexpr (IX) {
             // drop bit h from every mask; bit `last` becomes bit h, and the
             // masks of term `last` move to slot h
@@ -861,7 +860,7 @@ struct Walker {
         st(j, Z, nz);
         if constexpr (kFP) {
             const bool ni = set_fp(i, Y, fhash(ny, Y)), nj = set_fp(j, Z, fhash(nz, Z));
-            if constexpr (kClose) near = ni || nj;
+            near = ni || nj;
         }
         wave_lds_sync();
     }
@@ -939,10 +938,10 @@ struct Walker {
         uint32_t diff = ~0u;  // zero where a slot has it
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            if constexpr (kClose) diff = min(diff, fp[q][X] ^ h);
+            diff = min(diff, fp[q][X] ^ h);
             fp[q][X] = q * 64 + gl == k ? h : fp[q][X];
         }
-        const bool any = kClose && __ballot(diff == 0) != 0;
+        const bool any = __ballot(diff == 0) != 0;
         keep_apart<X>();
         return any;
     }
@@ -1135,11 +1134,9 @@ struct Walker {
         const uint32_t cb = ib < 0 ? 0u : two_shared_fp(h, 3, ib);
         ka = kb = -1;
         const bool any_a = __ballot(ca != 0) != 0, any_b = __ballot(cb != 0) != 0;
-        if constexpr (kClose) {
-            close |= ca | cb;
-            if (ia >= 0) set_close(ia, any_a);
-            if (ib >= 0) set_close(ib, any_b);
-        }
+        close |= ca | cb;
+        if (ia >= 0) set_close(ia, any_a);
+        if (ib >= 0) set_close(ib, any_b);
         if (!any_a && !any_b) return;  // the common case
         ka = first_merge_fp(ia, ca);
         kb = first_merge_fp(ib, cb);
@@ -1686,7 +1683,7 @@ struct Walker {
         }
         // U slots per round, their terms read before any is compared (indexes
         // clamped to the walk's rows), so the reads of a round overlap; the
-        // term-parallel kernels with four to seven slots read all at once
+        // term-parallel kernels with register slot copies read all at once
         constexpr int U = kRegSlots ? S : 2;
         const int qend = (wave_max_r() + G - 1) / G;
 #pragma unroll 1
@@ -1795,7 +1792,7 @@ struct Walker {
             const uint64_t cb = tr1 >= 0 ? two_shared(tr1) : 0ull;
             if ((ca | cb) == 0) return 0;
         }
-        if constexpr (kClose)
+        if constexpr (kFP)
             if (!near && !fp_stale && !may_be_close(tr0) && !may_be_close(tr1))
                 return 0;  // the common case
         bool done0 = tr0 < 0;
@@ -1891,7 +1888,7 @@ struct Walker {
 #pragma unroll 1
                 for (int x = 0; x < 3; ++x) refresh_one(j, x, false);
             }
-            if constexpr (kClose) {
+            if constexpr (kFP) {
 #pragma unroll 1
                 for (int x = 0; x < 3; ++x) find_close(x == 0 ? i : x == 1 ? j : nw);
             }
@@ -1908,7 +1905,7 @@ struct Walker {
     __device__ void load_scheme(const uint64_t *src, int rr)
     {
         fp_stale = true;
-        if constexpr (kClose) close = ~0u;
+        if constexpr (kFP) close = ~0u;
         for (int k = gl; k < rr; k += G)
 #pragma unroll
             for (int X = 0; X < 3; ++X) {
@@ -2084,7 +2081,7 @@ struct Walker {
             if (!additions) {
                 if (passes(1, a->t_reduce))
                     count(C_MERGES, (uint32_t)reduce(tr0, tr1));
-                else if constexpr (kClose)
+                else if constexpr (kFP)
                     close = near ? ~0u : close;
                 grow = passes(2, a->t_expand) && r <= best_rank + 2 && r < r_cap;
             }
@@ -2160,7 +2157,7 @@ struct Walker {
                     for (int X = 0; X < 3; ++X)
                         if (fp[q][X] != (k < rr ? fhash(f[X], X) : 0u)) bad |= TSF_CHECK_INDEX;
                 }
-            if (kClose && !additions)
+            if (!additions)
                 for (int k = gl; k < rr; k += G)
                     for (int j = 0; j < rr; ++j) {
                         if (j == k || (close >> (k >> 6) & 1u)) continue;
@@ -2477,7 +2474,7 @@ __device__ __forceinline__ void walk_body(const KArgs &a)
 // many as the LDS of 128 terms allows, although 15 registers go to scratch: a
 // round of 16,384 exploratory walks 6.90 ms at four per SIMD, 6.33 at five, 5.51
 // at six); the rest are not constrained (the term-parallel kernels with 64
-// lanes need 70 to 137).
+// lanes need 68 to 148).
 template <int G, int S, typename T, bool Z2, bool AP, bool IX, bool PK = false>
 __global__ void __launch_bounds__(256) __attribute__((
     amdgpu_waves_per_eu((PK || (AP && !IX && sizeof(T) == 4)) && G >= 8 ? 4
