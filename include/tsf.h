@@ -326,10 +326,10 @@ typedef struct {
  * term-parallel one).  waves_per_block: 1..4.  A zero field lets the library
  * choose: with all three zero a launch chosen by tsf_autotune for batches of
  * this shape, if there is one; with strategy and lanes_per_walk zero by
- * capacity, max_len and n_walks -- strategy 3 up to capacity 64 (32 lanes for
- * the smallest batches, 16 or 8 for larger ones), strategy 2 with 64 lanes for
- * small batches and large capacities, strategy 1 with 16 or 8 lanes for large
- * batches of up to 96 terms; with one of the two given, strategy 3 up to
+ * capacity, max_len, n_walks and objective -- strategy 3 up to capacity 64 (32
+ * lanes for the smallest batches, 16 or 8 for larger ones), strategy 2 with 64
+ * lanes for small batches and large capacities, strategy 1 with 16 or 8 lanes
+ * for large batches of up to 96 terms; with one of the two given, strategy 3 up to
  * capacity 64, 1 up to capacity 128 when max_len <= 32, 2 otherwise, and 8
  * lanes (64 for strategy 2); one wavefront per workgroup.
  * Results never depend on it. */

@@ -16,12 +16,12 @@
 // equation reachable; the search then takes its members in order, and a term's
 // set stays valid until the search leaves that term upwards.  LDS is sized by
 // the scheme's equations, so that a CU holds as many wavefronts as it has
-// slots.  16,384 subtrees of (2,2,3) schemes, 256 nodes each: 95-170 us a call
-// for most schemes, of which about 60 are its fixed cost (650-1,280 us with a
-// pattern at a time, every trial written to LDS and taken back, and 36 KiB of
-// LDS a wavefront); with 16,384 nodes each 0.8-4 ms (37-199 ms).  The first solution in the global order is the one in the
-// smallest subtree that has a solution, provided every smaller subtree was
-// searched to the end.
+// slots.  16,384 subtrees of (2,2,3) schemes, 256 nodes each: 85-190 us a call,
+// of which about 60 are its fixed cost (620-8,300 us with a pattern at a time,
+// every trial written to LDS and taken back, and 36 KiB of LDS a wavefront);
+// with 16,384 nodes each 0.16-2.5 ms (1.5-98 ms).  The first solution in the
+// global order is the one in the smallest subtree that has a solution, provided
+// every smaller subtree was searched to the end.
 #include <hip/hip_runtime.h>
 
 #include "../../include/tsf.h"
